@@ -465,8 +465,11 @@ __device__ __forceinline__ float column_sum(const float* v, int32_t W, int32_t K
 // j's thread also writes sums[j], the column sum of the rows in worker order.
 // Entry j starts the tiles after its predecessor's tile, up to its own (past the last entry the
 // tiles up to nt start at K).  A short run of tiles is written by its entry's thread; a longer one
-// (a gap in a message crowded into a few layers) by the whole workgroup as one coalesced run, after
-// each round (a thread writes its long run itself if the workgroup's list of them is full).
+// (a gap in a message crowded into a few layers) by a wavefront as one coalesced run, after each
+// round (a thread writes its long run itself if the workgroup's list of them is full).  The
+// workgroup's four wavefronts take the long runs in turn: by the whole workgroup one after another
+// the pass took 11.6 us over 16 top-k messages of ResNet-50's d whose gaps are hundreds of tiles,
+// now 8.3 us.
 // For ascending messages the entries' runs partition 0..nt.
 constexpr uint32_t kRunOwn = 32;        // runs of at most this many tiles are written by their own thread
                                         // (ResNet-50 top-k messages: 8.2 us with 128, 5.0 with 16-64)
@@ -497,7 +500,8 @@ __global__ __launch_bounds__(kNT) void k_agg_ranges(int32_t d, int32_t K, int32_
     // only a wavefront's first lane loads it (a second load of every entry doubled the requests
     // this pass makes of the caches: 1e8 elements, 16 messages at 10 %: 192 -> 146 us)
     uint32_t cur[kRangeU], prv[kRangeU];
-    const bool first = (threadIdx.x & 63u) == 0u;
+    const uint32_t lane = threadIdx.x & 63u;
+    const bool first = lane == 0u;
 #pragma unroll
     for (int u = 0; u < kRangeU; ++u) {
       const uint32_t j = j0 + (uint32_t)u * kNT + threadIdx.x;
@@ -542,14 +546,14 @@ __global__ __launch_bounds__(kNT) void k_agg_ranges(int32_t d, int32_t K, int32_
     }
     __syncthreads();
     const uint32_t nl = min(s_nlong, kRangeStash);
-    for (uint32_t q = 0; q < nl; ++q) {
+    for (uint32_t q = threadIdx.x / 64u; q < nl; q += kNT / 64u) {
       const uint32_t qa = s_ta[q], qe = qa + s_n[q], qj = s_j[q], qown = s_own[q];
       // 16-byte stores over the part of the run aligned in memory, single words at its two ends
       const uint32_t a4 = min(qe, qa + (uint32_t)((4u - (tbase + qa) % 4u) % 4u));
       const uint32_t b4 = a4 + (qe - a4) / 4u * 4u;
-      if (threadIdx.x < a4 - qa) ts[qa + threadIdx.x] = value(qj, qa + threadIdx.x, qown);
-      if (threadIdx.x < qe - b4) ts[b4 + threadIdx.x] = value(qj, b4 + threadIdx.x, qown);
-      for (uint32_t o = a4 + 4u * threadIdx.x; o < b4; o += 4u * kNT) {
+      if (lane < a4 - qa) ts[qa + lane] = value(qj, qa + lane, qown);
+      if (lane < qe - b4) ts[b4 + lane] = value(qj, b4 + lane, qown);
+      for (uint32_t o = a4 + 4u * lane; o < b4; o += 4u * 64u) {
         const uint4 v = make_uint4(value(qj, o, qown), value(qj, o + 1, qown), value(qj, o + 2, qown),
                                    value(qj, o + 3, qown));
         *reinterpret_cast<uint4*>(ts + o) = v;
@@ -591,30 +595,48 @@ struct AggOut {
   int32_t average;
 };
 
-__device__ __forceinline__ void agg_emit4(const AggOut& O, uint32_t i0, int nv, const float sum[4]) {
+__device__ __forceinline__ void agg_mean4(const AggOut& O, const float sum[4], float q[4]) {
   const bool pow2 = (O.wdiv & (O.wdiv - 1)) == 0;
   const float inv = 1.0f / (float)O.wdiv;  // exact when wdiv is a power of two
-  float q[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) q[j] = O.average ? agg_scale(sum[j], O.wdiv, pow2, inv) : sum[j];
+}
+
+__device__ __forceinline__ void agg_step4(const AggOut& O, const float q[4], float x[4], float m[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float dj = q[j];
+    if (O.wd != 0.0f) dj = dj + O.wd * x[j];
+    if (O.m) {
+      m[j] = O.beta * m[j] + dj;
+      dj = m[j];
+    }
+    x[j] = x[j] - dj;
+  }
+}
+
+__device__ __forceinline__ void agg_emit4(const AggOut& O, uint32_t i0, int nv, const float sum[4]) {
+  float q[4];
+  agg_mean4(O, sum, q);
   if (O.out) store4(O.out, i0, nv, q);
   if (O.x) {
     float x[4], m[4];
     load4(O.x, i0, nv, x);
     if (O.m) load4(O.m, i0, nv, m);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float dj = q[j];
-      if (O.wd != 0.0f) dj = dj + O.wd * x[j];
-      if (O.m) {
-        m[j] = O.beta * m[j] + dj;
-        dj = m[j];
-      }
-      x[j] = x[j] - dj;
-    }
+    agg_step4(O, q, x, m);
     store4(O.x, i0, nv, x);
     if (O.m) store4(O.m, i0, nv, m);
   }
+}
+
+// A whole group whose parameters and momentum are loaded already.
+__device__ __forceinline__ void agg_update4(const AggOut& O, uint32_t i0, const float sum[4], f4 xv, f4 mv) {
+  float q[4], x[4] = {xv.x, xv.y, xv.z, xv.w}, m[4] = {mv.x, mv.y, mv.z, mv.w};
+  agg_mean4(O, sum, q);
+  if (O.out) store4(O.out, i0, 4, q);
+  agg_step4(O, q, x, m);
+  store4(O.x, i0, 4, x);
+  if (O.m) store4(O.m, i0, 4, m);
 }
 
 constexpr int kAggChunk = 4;        // sparse aggregate: entries per lane loaded together past the first 64
@@ -697,17 +719,23 @@ __device__ __forceinline__ void agg_add_rest(AggLds& S, int nw, int w0, int32_t 
 }
 
 // Tiles whose workers hold more than this many entries each on average add them worker by worker
-// (agg_add_workers; 1e8 elements, 16 workers at 10 %: 414 -> 367 us, while at 1 %, about 10
-// entries per worker and tile, the staged form is twice as fast).
+// (agg_add_workers; BERT's d, 16 workers at 10 %: 316 us; at 1 %, about 10 entries per worker and
+// tile, the loads of one worker at a time leave five lanes in six idle and the staged form is
+// faster; 12, 16 and 24 in place of 48 measured the same within 1 % at 1, 3 and 10 %).
 constexpr uint32_t kAggDense = 48;
 constexpr int kAggW = 16;  // dense tiles: chunks of 64 entries loaded together
+constexpr int kAggJoint = 4;  // ... of which this many, if one worker's, are added together
 
 // Dense tiles: the group's workers one after another, in order.  A message holds each position at
 // most once, so the adds of one worker never collide: a chunk of up to 64 of one worker's entries
 // is added by its lanes at once, with no claims and no barriers (the one wavefront's LDS accesses
 // take effect in program order, so a position's adds run in worker order).  The chunks (worker by
 // worker, 64 entries each) are numbered through a prefix over the workers' chunk counts; kAggW
-// chunks are loaded together (coalesced), then added in order.
+// chunks are loaded together (coalesced), then added in order.  What bounds a dense tile is the
+// chain of LDS round trips: where kAggJoint chunks in a row are one worker's, their sums are read
+// together, added and written together (BERT's d, 16 workers at 10 %: 400 -> 316 us; ResNet-18's
+// d, 8 workers' top-k messages at 10 %: 30 -> 22 us).  (LDS float atomics, which would return
+// nothing to wait for, took 911 us there: they are processed a lane at a time.)
 __device__ __forceinline__ void agg_add_workers(AggLds& S, int nw, int w0, int32_t K, const uint32_t* idx,
                                                 const float* val, uint32_t lo, uint32_t hi) {
   const uint32_t lane = threadIdx.x;
@@ -719,21 +747,39 @@ __device__ __forceinline__ void agg_add_workers(AggLds& S, int nw, int w0, int32
   for (uint32_t q0 = 0; q0 < nch; q0 += kAggW) {
     uint32_t ci[kAggW];
     float cv[kAggW];
+    int cw[kAggW];
 #pragma unroll
     for (int u = 0; u < kAggW; ++u) {
       const uint32_t q = q0 + (uint32_t)u;
       // chunk q's worker: the last one whose chunks start at or before q (wave-uniform)
       const int w = (int)__popcll(__ballot(lane < (uint32_t)nw && cpre <= q)) - 1;
-      const uint32_t f = (q - __shfl(cpre, w, 64)) * 64u + lane;
-      const bool ok = q < nch && f < __shfl(n, w, 64);
-      const size_t j = (size_t)(w0 + w) * K + __shfl(a, w, 64) + f;
-      ci[u] = ok ? idx[j] : 0u;
+      const uint32_t f = (q - (uint32_t)__builtin_amdgcn_readlane((int)cpre, w)) * 64u + lane;
+      const bool ok = q < nch && f < (uint32_t)__builtin_amdgcn_readlane((int)n, w);
+      const size_t j = (size_t)(w0 + w) * K + (uint32_t)__builtin_amdgcn_readlane((int)a, w) + f;
+      ci[u] = ok ? idx[j] : hi;  // hi: adds nothing below
       cv[u] = ok ? val[j] : 0.0f;
-      if (!ok) ci[u] = hi;  // adds nothing below
+      cw[u] = w;
     }
+    // Four chunks of one worker (their positions differ): their sums are read together, not one
+    // after another's write.
 #pragma unroll
-    for (int u = 0; u < kAggW; ++u)
-      if (ci[u] >= lo && ci[u] < hi) S.acc[ci[u] - lo] += cv[u];
+    for (int u = 0; u < kAggW; u += kAggJoint) {
+      if (cw[u] == cw[u + kAggJoint - 1]) {
+        float t[kAggJoint];
+#pragma unroll
+        for (int v = 0; v < kAggJoint; ++v) {
+          const uint32_t x = ci[u + v] - lo;
+          t[v] = S.acc[x < kAggTile ? x : 0u];
+        }
+#pragma unroll
+        for (int v = 0; v < kAggJoint; ++v)
+          if (ci[u + v] >= lo && ci[u + v] < hi) S.acc[ci[u + v] - lo] = t[v] + cv[u + v];
+      } else {
+#pragma unroll
+        for (int v = u; v < u + kAggJoint; ++v)
+          if (ci[v] >= lo && ci[v] < hi) S.acc[ci[v] - lo] += cv[v];
+      }
+    }
   }
 }
 
@@ -753,6 +799,10 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n) {
   return base + x * q + min(x, r) + (j - full);
 }
 
+// UPD: with the parameter update.  A whole tile's parameters and momentum are then loaded along with
+// the ranges, so that the update waits for no third round trip at the end (8 workers at 1 % on
+// ResNet-18's d with momentum: 42.7 -> 34.8 us; 187 MB at least, 29 us).
+template <bool UPD>
 __global__ __launch_bounds__(64) void k_agg_sparse(int32_t d, int32_t W, int32_t K, int32_t nt,
                                                    const uint32_t* idx, const float* val,
                                                    const uint32_t* tile_start, AggOut O) {
@@ -764,9 +814,19 @@ __global__ __launch_bounds__(64) void k_agg_sparse(int32_t d, int32_t W, int32_t
   const int nw0 = min(W, 64);
   const uint32_t* ts = tile_start + (size_t)min(lane, nw0 - 1) * (nt + 1) + t;
   const uint32_t ra = ts[0], rb = ts[1];
+  const bool ahead = UPD && hi - lo == kAggTile;
+  f4 xv[UPD ? kAggRounds : 1], mv[UPD ? kAggRounds : 1];
+  if (ahead) {
+#pragma unroll
+    for (int r = 0; r < (UPD ? kAggRounds : 0); ++r) {
+      const uint32_t i0 = lo + (uint32_t)(r * 64 + lane) * 4u;
+      xv[r] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(O.x + i0));
+      if (O.m) mv[r] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(O.m + i0));
+    }
+  }
   for (uint32_t x = lane; x < kAggClaim; x += 64) S.claim[x] = ~0u;
   const uint32_t E = agg_group(S, nw0, K, ra, rb);
-  if (W <= 64 && E == 0) {
+  if (W <= 64 && E == 0 && !ahead) {
 #pragma unroll
     for (int r = 0; r < kAggRounds; ++r) {
       const uint32_t i0 = lo + (uint32_t)(r * 64 + lane) * 4u;
@@ -799,7 +859,8 @@ __global__ __launch_bounds__(64) void k_agg_sparse(int32_t d, int32_t W, int32_t
     const int n = i0 < hi ? (int)min(4u, hi - i0) : 0;
     const f4 s4 = *reinterpret_cast<const f4*>(&S.acc[x]);
     const float v[4] = {s4.x, s4.y, s4.z, s4.w};
-    agg_emit4(O, i0, n, v);
+    if (UPD && ahead) agg_update4(O, i0, v, xv[UPD ? r : 0], mv[UPD ? r : 0]);
+    else agg_emit4(O, i0, n, v);
   }
 }
 

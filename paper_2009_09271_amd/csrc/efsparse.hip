@@ -1187,8 +1187,9 @@ int run_aggregate(const ef_layout* L, int msg_kind, int32_t W, const uint32_t* m
       EF_LAUNCH(k_agg_ranges<1>, dim3((unsigned)blocks, (unsigned)W), blk, 0, st, L->T.d, (int32_t)L->K, nt, m, ts,
                 (uint64_t)(nt + 1), val, vW, sums);
     EF_TRY(launched());
-    EF_LAUNCH(k_agg_sparse, dim3((unsigned)nt), dim3(64), 0, st, L->T.d, W, (int32_t)L->K, nt, m,
-              sums ? sums : val, ts, O);
+    const float* v = sums ? sums : val;
+    if (O.x) EF_LAUNCH(k_agg_sparse<true>, dim3((unsigned)nt), dim3(64), 0, st, L->T.d, W, (int32_t)L->K, nt, m, v, ts, O);
+    else EF_LAUNCH(k_agg_sparse<false>, dim3((unsigned)nt), dim3(64), 0, st, L->T.d, W, (int32_t)L->K, nt, m, v, ts, O);
     return launched();
   }
   if (msg_kind == EF_MSG_BLOCK) {
