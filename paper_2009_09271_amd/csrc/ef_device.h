@@ -48,8 +48,9 @@ enum : int {
   R_RETRY = 9,  // top-k: 1 when the segment's candidates fell short of k_l and are collected again
   R_A2 = 10,    // top-k retry: the lower threshold; keys in (R_A2, R_A) are the listed candidates,
                 //   keys equal to it are counted
-  R_OVF = 11,   // top-k: candidates did not fit the workspace (a retry collects them again, else the
+  R_OVF = 11,   // candidates did not fit the workspace (top-k: a retry collects them again, else the
                 //   exact path runs)
+  R_DONE = 12,  // top-k, many rows: the rows' winner counts are complete (k_rowcount has nothing to do)
 };
 
 constexpr int kBtWords = 8;  // words per record of the block aggregate's (tile, segment) table
@@ -285,6 +286,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   v = dpp_add<0x118, 0xF>(v);  // row_shr:8
   v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
   return dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+}
+
+// Inclusive sums over each row of 16 lanes, and the sum of lanes 0-7 (uniform).
+__device__ __forceinline__ uint32_t row16_incl_scan(uint32_t v) {
+  v = dpp_add<0x111, 0xF>(v);
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  return dpp_add<0x118, 0xF>(v);
+}
+__device__ __forceinline__ uint32_t row8_sum(uint32_t v) {
+  v = dpp_add<0x111, 0xF>(v);
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 7);
 }
 
 // Exclusive scan over the workgroup (NT threads) in thread order; `lds` holds NT/64 words.  Two

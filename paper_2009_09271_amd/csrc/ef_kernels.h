@@ -14,14 +14,16 @@
 //                    the rule above; random-k: Philox key < tau_l, a binomial bound on k_l), the
 //                    row's candidates in index order to its slot, and a histogram of them (top-k).
 //                    Random-k on layouts whose rows and key window fit k_select's LDS: also the
-//                    row's certain winners (key < ulo_l) counted and its undecided candidates
-//                    listed, so that k_collect is not needed.
+//                    row's undecided candidates (key in [ulo_l, tau_l)) listed, so that
+//                    k_collect_randk is not needed.
 //   k_resolve        top-k, per segment: the histogram bin holding the k_l-th best candidate.
-//   k_collect        per row: candidates above that bin (random-k: key below ulo_l) are counted,
-//                    the undecided ones are listed.
+//   k_collect        top-k, per row: candidates above that bin are counted, the undecided ones are
+//                    listed (random-k without direct lists: k_collect_randk).
 //   k_select         per segment: the exact threshold among the listed candidates, then the
-//                    message offset of every row.  Layouts with a very large k_l instead count
-//                    and scan the rows' winners in k_rowcount and k_rowscan.
+//                    message offset of every row.  Layouts with a very large k_l or very many
+//                    rows instead add the list's winners to the rows' counts, which k_rowsum
+//                    scans (a list too long for that: k_rowcount counts again, k_rowtie
+//                    resolves ties at the threshold).
 //   k_emit           per row: the winners in index order to the message and e = +0 there (where
 //                    the pass already stored +0 at every candidate, random-k and dense top-k
 //                    segments, the losing candidates get their values back instead).
@@ -50,12 +52,17 @@ struct WSel {
   uint32_t* roff;      // [nrows] message position of each row's first winner
   uint32_t* rtie;      // [nrows] top-k: elements equal to the key A (counted, not stored)
   uint32_t* lcnt;      // [L][kSubLists][kLineWords] sizes of the sub-lists, one cache line each
+  uint32_t* scnt;      // [L][kSubLists][kLineWords] random-k without direct lists: certain winners of the
+                       //   segment's rows (row r adds to counter r % 16)
+  uint32_t* bsum;      // [kRowBlocks] many-row layouts: winners of each block of rows
   uint32_t* coff;      // [nrows] first entry of each row's candidates in the pool (kDropped: not
                        //   stored); one segment: written only for rows beyond their static slot
   uint32_t* pcnt;      // [kPools][kLineWords] fill counters of the overflow pool's parts
-  uint32_t* cand_idx;  // [pool0 + capB] candidate pool: each row's static slot (soff, S),
-  float* cand_val;     //   then the overflow pool for rows with more candidates (index order per row)
-  uint32_t* cand_key;  //   key' of each candidate
+  uint16_t* cand_loc;  // [pool0 + capB] candidate pool: each row's static slot (soff, S), then the overflow
+  float* cand_val;     //   pool for rows with more candidates (index order per row): a candidate's element
+                       //   within the row's data tile (random-k: kCertain added when its key is below
+                       //   ulo) and its value.  Top-k's key' is the value's magnitude
+  uint32_t* cand_key;  //   random-k: key' of the candidates without kCertain
   uint32_t* list_idx;  // sub-lists of undecided candidates, per segment (see SubLists)
   uint32_t* list_key;
   uint2* pairs;        // random-k, direct layouts: each row's undecided (key', index) pairs at its
@@ -70,7 +77,10 @@ struct WSel {
 constexpr uint32_t kDropped = 0xFFFFFFFFu;  // coff of a row whose candidates did not fit
 constexpr uint32_t kAccRow = 0x80000000u;   // counts flag of a top-k row emitted from acc (winning
                                             //   ties); the count is then the row's length
+constexpr uint32_t kCertain = 0x8000u;      // cand_loc flag
 constexpr int kPools = 16;                  // parts of the overflow pool, one counter each
+constexpr uint32_t kRowBlocks = 256;        // many-row layouts: blocks of rows (at most) whose winners are
+                                            //   scanned by themselves
 
 __device__ __forceinline__ uint32_t* res_of(const WSel& w, int l) { return w.res + (size_t)l * kResWords; }
 
@@ -104,9 +114,11 @@ __device__ __forceinline__ WSel ws_at(WSel w, uint64_t off) {
   w.roff = shifted(w.roff, off);
   w.rtie = shifted(w.rtie, off);
   w.lcnt = shifted(w.lcnt, off);
+  w.scnt = shifted(w.scnt, off);
+  w.bsum = shifted(w.bsum, off);
   w.coff = shifted(w.coff, off);
   w.pcnt = shifted(w.pcnt, off);
-  w.cand_idx = shifted(w.cand_idx, off);
+  w.cand_loc = shifted(w.cand_loc, off);
   w.cand_val = shifted(w.cand_val, off);
   w.cand_key = shifted(w.cand_key, off);
   w.list_idx = shifted(w.list_idx, off);
@@ -118,6 +130,13 @@ __device__ __forceinline__ WSel ws_at(WSel w, uint64_t off) {
 constexpr int kLineWords = 32;  // 128-byte L2 line: counters hit by many atomics get a line each
 __device__ __forceinline__ uint32_t* lcnt_of(const WSel& w, int l, uint32_t c) {
   return w.lcnt + ((size_t)l * kSubLists + c) * kLineWords;
+}
+__device__ __forceinline__ uint32_t* scnt_of(const WSel& w, int l, uint32_t c) {
+  return w.scnt + ((size_t)l * kSubLists + c) * kLineWords;
+}
+// The first element of a row's data tile.
+__device__ __forceinline__ uint32_t row_tile(const Tables& T, uint32_t row) {
+  return T.L == 1 ? row * kTile : T.row_rec[4u * (size_t)row + 3u];
 }
 __device__ __forceinline__ uint32_t* pcnt_of(const WSel& w, uint32_t part) { return w.pcnt + (size_t)part * kLineWords; }
 
@@ -1099,11 +1118,11 @@ constexpr uint32_t kRankList = 256;    // lists up to this size are ranked direc
 constexpr uint32_t kBigK = 1u << 20;   // layouts with a k_l this large count row winners in parallel
 constexpr int32_t kBigRows = 16384;    // ... and so do layouts with a segment of more rows than this
 constexpr uint32_t kSelPer = 8;        // rows per k_select thread held in registers
-constexpr uint32_t kHistDirect = 32;   // rows with more candidates histogram them in LDS first
+constexpr uint32_t kHistDirect = 32;   // rows with more candidates below the last bin histogram them in LDS first
 constexpr int kHCopies = 16;           // copies of each candidate histogram (row r adds to copy r % 16)
 constexpr uint32_t kDiagCount = 4u;    // diagnostics: the row counts of a segment did not add up to k_l
 // R_IT of a top-k segment on a many-row layout whose threshold key T is shared by more listed
-// candidates than win: k_rowcount counts each row's keys equal to T, k_rowscan finds the last
+// candidates than win: k_rowcount counts each row's keys equal to T, k_rowtie finds the last
 // winner among them (R_NEED of them win, in index order) and writes the real R_IT.
 constexpr uint32_t kTieRows = 0xFFFFFFFEu;
 
@@ -1327,6 +1346,12 @@ __device__ __forceinline__ uint32_t cand_bin(uint32_t key, uint32_t A, uint32_t 
   return key == A ? 0u : 1u + min((key - A - 1u) >> sh, (uint32_t)kHBins - 2u);
 }
 
+// The least key of the last bin (a key the bins cannot reach: 2^32 - 1, above every magnitude).
+__device__ __forceinline__ uint32_t last_bin_key(uint32_t A, uint32_t sh) {
+  const uint64_t t = (uint64_t)A + 1u + ((uint64_t)(kHBins - 2u) << sh);
+  return (uint32_t)min<uint64_t>(t, 0xFFFFFFFFull);
+}
+
 // Magnitude keys of acc read in place (a row's elements equal to A are counted, not stored).
 struct AccKeys {
   const float* p;
@@ -1508,7 +1533,10 @@ __global__ __launch_bounds__(kSelNT) void k_sample_select(Tables T, WSel ws0, Ba
   uint32_t top = rank_edge(bin_u, above_u, urank, true);
   if (top <= thr || top > kmax) top = kmax;
   const uint32_t span = top - thr;
-  const uint32_t sh = span < 1024u ? 0u : (uint32_t)(32 - __clz(span)) - 10u;
+  // the least shift whose bins 1 .. kHBins - 2 hold the span (2^11 - 2 of them: span < 2^b gives at
+  // most 2^10 bins with a shift of b - 10, and one bit less where that still fits)
+  uint32_t sh = span < 1024u ? 0u : (uint32_t)(32 - __clz(span)) - 10u;
+  if (sh && (span >> (sh - 1u)) < (uint32_t)kHBins - 2u) --sh;
   if (threadIdx.x == 0) {
     R[R_A] = thr;
     R[R_IA] = 0xFFFFFFFFu;
@@ -1521,9 +1549,7 @@ __global__ __launch_bounds__(kSelNT) void k_sample_select(Tables T, WSel ws0, Ba
 
 // ---------------------------------------------------------------------------------------------
 // Streaming pass: fused accumulate + candidate test + ordered compaction into the row's slot
-// (+ top-k: candidate histogram).  One workgroup of kStrNT threads per row, one float4 group per
-// thread (short-lived workgroups keep the end of the grid short, where a streaming pass loses
-// bandwidth).
+// (+ top-k: candidate histogram).  One workgroup of kStrNT threads per row.
 // ---------------------------------------------------------------------------------------------
 // Threads per workgroup of the streaming selection pass: two float4 groups per thread (a row of
 // kTile elements per workgroup).  Measured per pass on ResNet-50 flat, top-k / random-k: 256
@@ -1532,18 +1558,259 @@ __global__ __launch_bounds__(kSelNT) void k_sample_select(Tables T, WSel ws0, Ba
 constexpr int kStrNT = 512;
 constexpr int kStrW = kStrNT / 64;     // its wavefronts
 
-// ZC: some top-k segment of the layout has seg_zc (the form without it has no such test).
-template <int KIND, int GDT, bool FUSED, bool ZC = false>
+// Its LDS.
+template <int KIND>
+struct StreamLds {
+  uint32_t wt[16];                          // candidates by group and wavefront (group-major)
+  uint32_t tie[8];                          // top-k: elements equal to A, and candidates of the last bin << 16
+  uint32_t cert[8];                         // random-k: certain winners by wavefront
+  uint32_t und;                             // random-k, direct lists: undecided candidates listed so far
+  uint32_t cb;                              // the row's first pool entry (a reservation in the overflow pool)
+  uint32_t hist[KIND == 0 ? kHBins : 1];
+};
+
+// The pass is close to being bound by its instructions (a row's 48 KB pass a CU in about 4700 cycles),
+// so what a row's lanes share is kept in scalar registers: candidate sets as lane masks (a compare's
+// own result), counts as their population counts.  WHOLE: the row is a whole data tile (all but a
+// segment's ends): no element is masked.  Candidates take six bytes (value, place in the tile), top-k's
+// keys being the values' magnitudes.  Against per-lane flags, masks on every row and twelve-byte
+// candidates: 1e9 elements at 1 %, random-k, bf16 1727 -> 1602 us (10.1 GB, 1575 us at the 6.4 TB/s
+// that plain streaming reaches); BERT per layer at 1 %, top-k, bf16 216 -> 198 us (172), flat at 10 %
+// 264 -> 234 us (219); ResNet-18 per layer at 1 %, random-k 27.6 -> 25.7 us (22).
+// (Measured and slower: candidates staged in LDS and stored by coalesced instructions, with the
+// histogram cleared and counted before the row's barrier, BERT per layer 210 -> 218 us, for its two
+// more barriers; histogram rows of up to 256 keys added to global memory without LDS, 218 -> 395 us.)
+template <int KIND, int GDT, bool FUSED, bool ZC, bool DIRECT, bool WHOLE>
+__device__ __forceinline__ void stream_row(const Tables& T, const void* g, const float* src, float* acc_out, uint32_t s0,
+                                           uint32_t s1, uint32_t step, const WSel& ws, StreamLds<KIND>& S, uint32_t row,
+                                           int l, uint32_t o, uint32_t tb, uint32_t lo, uint32_t hi, uint32_t cb,
+                                           uint32_t scap) {
+  constexpr int kSR = (int)kTile / (4 * kStrNT);  // float4 groups per thread
+  static_assert(kSR * kStrW == 16 && kStrW == 8, "a row's counts fit 16 lanes");
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  uint32_t* R = res_of(ws, l);
+  uint32_t mode = 1, A = 0, IA = 0, sh = 0, ulo = 0, tlast = 0;
+  bool zc = false;  // top-k, fused: +0 stored at the candidates, not acc
+  if constexpr (KIND == 0) {
+    mode = R[R_MODE];
+    A = R[R_A];
+    IA = R[R_IA];
+    sh = R[R_SH];
+    zc = ZC && FUSED && T.seg_zc[l] != 0u;
+  } else {
+    tlast = (uint32_t)(T.seg_tau[l] - 1u);  // the largest candidate key
+    ulo = T.seg_ulo[l];
+    // the counters of k_collect_randk start from zero (this kernel completes before it runs)
+    if (!DIRECT && tb == o / kTile * kTile) {
+      if (threadIdx.x < kSubLists) *lcnt_of(ws, l, threadIdx.x) = 0u;
+      else if (threadIdx.x < 2 * kSubLists) *scnt_of(ws, l, threadIdx.x - kSubLists) = 0u;
+      else if (threadIdx.x == 2 * kSubLists) R[R_OVF] = 0u;
+    }
+  }
+  float v[kSR][4];
+  uint32_t vm[kSR];
+  uint32_t i0[kSR];
+#pragma unroll
+  for (int r = 0; r < kSR; ++r) {
+    i0[r] = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
+    vm[r] = WHOLE ? 0xFu : group_mask(i0[r], lo, hi);
+  }
+  auto in = [&](int r, int q) { return WHOLE || ((vm[r] >> q) & 1u); };
+  auto store = [&](int r, const float x[4]) {
+    if constexpr (WHOLE) store4(acc_out, i0[r], 4, x);
+    else store4m(acc_out, i0[r], vm[r], x);
+  };
+  float gv[kSR][4];
+  const bool data = !(KIND == 1 && !FUSED && !src);  // none: a random-k selection prepared ahead of the step
+#pragma unroll
+  for (int r = 0; r < kSR; ++r) {
+    if constexpr (FUSED) {
+      if constexpr (WHOLE) load4gf<GDT>(g, i0[r], gv[r]);
+      else load4gm<GDT>(g, i0[r], vm[r], gv[r]);
+    }
+    if (data) {
+      if constexpr (WHOLE) load4f(src, i0[r], v[r]);
+      else load4m(src, i0[r], vm[r], v[r]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[r][q] = 0.0f;
+    }
+  }
+  // random-k: the Philox keys of the thread's elements depend on positions only; they are computed
+  // while the thread's loads are in flight
+  uint32_t uk[KIND == 1 ? kSR : 1][4];
+  if constexpr (KIND == 1) {
+#pragma unroll
+    for (int r = 0; r < kSR; ++r) {
+      if ((o & 3u) == 0) {  // the float4 group is one Philox block
+        uint4 x = make_uint4(0u, 0u, 0u, 0u);
+        if (vm[r]) x = philox(make_uint4((i0[r] - o) >> 2, 0u, step, kRandkTag | (uint32_t)l), s0, s1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) uk[r][q] = word(x, q);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) uk[r][q] = in(r, q) ? randk_key(i0[r] + q - o, (uint32_t)l, step, s0, s1) : 0u;
+      }
+    }
+  }
+  uint64_t cm[kSR][4];   // the wavefront's candidates
+  uint64_t wm[KIND == 1 ? kSR : 1][4];  // random-k: those that are certain winners (key below ulo)
+  uint32_t n[kSR];       // their number
+  uint32_t ncert = 0, ntie = 0, nlast = 0;
+  const uint32_t top = ZC ? last_bin_key(A, sh) : 0xFFFFFFFFu;
+#pragma unroll
+  for (int r = 0; r < kSR; ++r) {
+    if constexpr (FUSED) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[r][q] = gv[r][q] + v[r][q];
+      if (KIND == 0 && !zc) store(r, v[r]);
+    }
+    n[r] = 0;
+    float z[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      bool c;
+      if constexpr (KIND == 0) {
+        // sampled segments: keys above A are stored, keys equal to A (the tie bin: exact zeros, say,
+        // which may be most of a segment) only counted; exact segments: the winner rule itself
+        const uint32_t k = mag_key(v[r][q]);
+        const uint64_t gt = __ballot(in(r, q) && k > A), eq = __ballot(in(r, q) && k == A);
+        cm[r][q] = gt;
+        if (mode == 0) {
+          ntie += (uint32_t)__popcll(eq);
+          if constexpr (ZC) nlast += (uint32_t)__popcll(__ballot(in(r, q) && k >= top));
+        } else if (eq) {
+          cm[r][q] = gt | __ballot(in(r, q) && k == A && i0[r] + q < IA);
+        }
+        c = __builtin_amdgcn_inverse_ballot_w64(cm[r][q]);
+      } else {
+        c = in(r, q) && uk[r][q] <= tlast;
+        cm[r][q] = __ballot(c);
+        wm[r][q] = __ballot(in(r, q) && uk[r][q] < ulo);
+        ncert += (uint32_t)__popcll(wm[r][q]);
+      }
+      n[r] += (uint32_t)__popcll(cm[r][q]);
+      z[q] = c ? 0.0f : v[r][q];
+    }
+    // +0 stored at the candidates, whose losers the emission restores: random-k (the window's losers
+    // are few, about 6 sqrt(k_l) + 32 of a segment; zeroing the winners afterwards instead wrote
+    // single words into lines long evicted from the caches: 1e9 elements at 10 %, 1.9 of the
+    // emission's 2.3 ms) and top-k segments with seg_zc.  The exact path puts them all back first.
+    if (FUSED && (KIND == 1 || zc)) store(r, z);
+    if (lane == 0) S.wt[r * kStrW + wid] = n[r];
+  }
+  if (lane == 0) {
+    if constexpr (KIND == 1) S.cert[wid] = ncert;
+    else S.tie[wid] = ntie | (nlast << 16);  // (a wavefront has 512 elements)
+  }
+  if (KIND == 1 && threadIdx.x == 0) S.und = 0;
+  __syncthreads();
+  // the row's candidates go to its static slot, or, when there are more than it holds, to entries
+  // reserved in the overflow pool; a row that does not fit is dropped and its segment takes the
+  // exact path (the histogram still counts its candidates)
+  const uint32_t cnt16 = S.wt[lane & 15u], side = KIND == 0 ? S.tie[lane & 7u] : S.cert[lane & 7u];
+  const uint32_t inc = row16_incl_scan(cnt16);
+  const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 15);
+  const uint32_t all = row8_sum(side);  // ties | last << 16; certain winners
+  if (tot > scap) {
+    if (threadIdx.x == 0) S.cb = pool_reserve(ws, row, tot);
+    __syncthreads();
+    cb = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.cb);
+  }
+  const bool dropped = cb == kDropped;
+  if (threadIdx.x == 0) {
+    if (T.L > 1 || tot > scap) ws.coff[row] = cb;
+    ws.counts[row] = tot;
+    if (KIND == 1) ws.rcnt[row] = all;  // its certain winners (key below ulo)
+  }
+  if (dropped) {
+    if constexpr (KIND == 0) {
+      if (threadIdx.x == 0) atomicOr(&R[R_OVF], 1u);
+    }
+    if (FUSED && (KIND == 1 || zc)) {
+      // the candidates' values were stored as +0 above; without the candidates the exact path
+      // cannot restore them, so they are stored again now
+#pragma unroll
+      for (int r = 0; r < kSR; ++r) store(r, v[r]);
+    }
+  }
+  uint32_t* gh = KIND == 0 ? ws.hist + ((size_t)l * kHCopies + (row % kHCopies)) * kHBins : nullptr;
+  if (KIND == 0 && mode == 0 && threadIdx.x == 0) {
+    // the ties are the histogram's bin 0
+    const uint32_t tie = all & 0xFFFFu, last = all >> 16;
+    ws.rtie[row] = tie;
+    if (tie) atomicAdd(gh, tie);
+    if (ZC && last) atomicAdd(gh + kHBins - 1, last);
+  }
+#pragma unroll
+  for (int r = 0; r < kSR; ++r) {
+    if (n[r] && !dropped) {  // uniform
+      uint32_t pos = cb + (uint32_t)__builtin_amdgcn_readlane((int)(inc - cnt16), (int)(r * kStrW + wid));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) pos += lanes_below(cm[r][q]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (__builtin_amdgcn_inverse_ballot_w64(cm[r][q])) {
+          const uint32_t x = i0[r] - tb + q;
+          const bool certain = KIND == 1 && __builtin_amdgcn_inverse_ballot_w64(wm[r][q]);
+          ws.cand_loc[pos] = (uint16_t)(certain ? x | kCertain : x);
+          ws.cand_val[pos] = v[r][q];
+          if (KIND == 1 && !certain) {
+            const uint32_t key = ~uk[r][q];
+            ws.cand_key[pos] = key;
+            if constexpr (DIRECT) {
+              // direct lists: (key', index) pairs at the row's pool entries in the pair array (fewer
+              // than its candidates)
+              const uint32_t p = atomicAdd(&S.und, 1u);
+              ws.pairs[(size_t)cb + p] = make_uint2(key, tb + x);
+            }
+          }
+          ++pos;
+        }
+      }
+    }
+  }
+  if constexpr (KIND == 0) {
+    const uint32_t below = tot - (ZC ? all >> 16 : 0u);  // candidates below the last bin (without ZC: all)
+    if (mode == 0 && below) {
+      if (below > kHistDirect) {  // many: count them in LDS, then one atomic per used bin
+        for (int b = threadIdx.x; b < kHBins; b += kStrNT) S.hist[b] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSR; ++r)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (n[r] && __builtin_amdgcn_inverse_ballot_w64(cm[r][q])) {
+              const uint32_t k = mag_key(v[r][q]);
+              if (!ZC || k < top) atomicAdd(&S.hist[cand_bin(k, A, sh)], 1u);
+            }
+        __syncthreads();
+        for (int b = threadIdx.x; b < kHBins; b += kStrNT) {
+          const uint32_t c = S.hist[b];
+          if (c) atomicAdd(&gh[b], c);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < kSR; ++r)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (n[r] && __builtin_amdgcn_inverse_ballot_w64(cm[r][q])) {
+              const uint32_t k = mag_key(v[r][q]);
+              if (!ZC || k < top) atomicAdd(&gh[cand_bin(k, A, sh)], 1u);
+            }
+      }
+    }
+  }
+}
+
+// ZC: some top-k segment of the layout has seg_zc (the form without it has no such test, nor the last
+// bin's count by ballot: the last bin holds most of a dense segment's candidates, few of the others').
+// DIRECT: random-k with direct lists (T.rk_direct).
+template <int KIND, int GDT, bool FUSED, bool ZC = false, bool DIRECT = false>
 __global__ __launch_bounds__(kStrNT) void k_stream_sel(Tables T, const void* g, const float* src, float* acc_out,
                                                     uint32_t s0, uint32_t s1, uint32_t step, WSel ws) {
-  constexpr int kSR = (int)kTile / (4 * kStrNT);  // float4 groups per thread
-  __shared__ uint32_t wt[kSR][kStrW];
-  __shared__ uint32_t s_hist[KIND == 0 ? kHBins : 1];
-  __shared__ uint32_t s_kk[KIND == 1 ? kTile : 1];  // random-k: the candidates' keys, by element
-  __shared__ uint32_t wc[kStrW];  // random-k, direct lists: certain winners per wavefront
-  __shared__ uint32_t s_und;         // random-k, direct lists: undecided candidates listed so far
-  __shared__ uint32_t s_tie[KIND == 0 ? kStrW : 1];  // top-k: elements equal to A per wavefront
-  __shared__ uint32_t s_cb;          // the row's first pool entry (a reservation in the overflow pool)
+  __shared__ StreamLds<KIND> S;
   const uint32_t row = blockIdx.x;
   // the row's segment and bounds: arithmetic on one segment, else one record load (the data loads
   // wait for the bounds only, not for a chain through the segment tables)
@@ -1563,286 +1830,10 @@ __global__ __launch_bounds__(kStrNT) void k_stream_sel(Tables T, const void* g, 
     static_slot(T, ws, row, cb, scap);
   }
   const uint32_t lo = max(o, tb), hi = min(e_, tb + kTile);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  uint32_t* R = res_of(ws, l);
-  uint32_t mode = 1, A = 0, IA = 0, sh = 0, ulo = 0;
-  uint64_t tau = 0;
-  const bool direct = KIND == 1 && T.rk_direct;
-  bool zc = false;  // top-k, fused: +0 stored at the candidates, not acc
-  if constexpr (KIND == 0) {
-    mode = R[R_MODE];
-    A = R[R_A];
-    IA = R[R_IA];
-    sh = R[R_SH];
-    zc = ZC && FUSED && T.seg_zc[l] != 0u;
-  } else {
-    tau = T.seg_tau[l];
-    ulo = T.seg_ulo[l];
-    // the list counter of k_collect starts from zero (this kernel completes before it runs)
-    if (!direct && tb == o / kTile * kTile && threadIdx.x < kSubLists) *lcnt_of(ws, l, threadIdx.x) = 0;
-  }
-
-  float v[kSR][4];
-  uint32_t vm[kSR];
-#pragma unroll
-  for (int r = 0; r < kSR; ++r) vm[r] = group_mask(tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u, lo, hi);
-  const bool whole = lo == tb && hi == tb + kTile;  // the row is the whole tile (uniform)
-  // random-k: the Philox keys of the thread's elements depend on positions only; they are computed
-  // while the thread's loads are in flight (called right after the loads are issued)
-  uint32_t uk[KIND == 1 ? kSR : 1][4];
-  auto random_keys = [&]() {
-    if constexpr (KIND == 1) {
-#pragma unroll
-      for (int r = 0; r < kSR; ++r) {
-        const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-        if ((o & 3u) == 0) {  // the float4 group is one Philox block
-          uint4 x = make_uint4(0u, 0u, 0u, 0u);
-          if (vm[r]) x = philox(make_uint4((i0 - o) >> 2, 0u, step, kRandkTag | (uint32_t)l), s0, s1);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) uk[r][q] = word(x, q);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            uk[r][q] = ((vm[r] >> q) & 1u) ? randk_key(i0 + q - o, (uint32_t)l, step, s0, s1) : 0u;
-        }
-      }
-    }
-  };
-  if constexpr (FUSED) {
-    float gv[kSR][4];
-    if (whole) {
-#pragma unroll
-      for (int r = 0; r < kSR; ++r) {
-        const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-        load4gf<GDT>(g, i0, gv[r]);
-        load4f(src, i0, v[r]);
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < kSR; ++r) {
-        const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-        load4gm<GDT>(g, i0, vm[r], gv[r]);
-        load4m(src, i0, vm[r], v[r]);
-      }
-    }
-    random_keys();
-#pragma unroll
-    for (int r = 0; r < kSR; ++r) {
-      const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[r][q] = gv[r][q] + v[r][q];
-      // top-k: stored at once (+0 at the candidates where seg_zc asks for it: the candidate rule
-      // needs only the key); random-k: stored below, once the candidates are known
-      if constexpr (KIND == 0) {
-        if (zc) {
-          float o[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const uint32_t k = mag_key(v[r][q]);
-            o[q] = k > A || (mode != 0 && k == A && i0 + q < IA) ? 0.0f : v[r][q];
-          }
-          store4m(acc_out, i0, vm[r], o);
-        } else {
-          store4m(acc_out, i0, vm[r], v[r]);
-        }
-      }
-    }
-  } else if (KIND == 1 && !src) {
-    // random-k without data (a selection prepared ahead of the step): keys and positions only
-#pragma unroll
-    for (int r = 0; r < kSR; ++r)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[r][q] = 0.0f;
-    random_keys();
-  } else {
-#pragma unroll
-    for (int r = 0; r < kSR; ++r) {
-      const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-      if (whole) load4f(src, i0, v[r]);
-      else load4m(src, i0, vm[r], v[r]);
-    }
-    random_keys();
-  }
-  // candidate flags; wave-level prefixes through ballots, one barrier for the whole row
-  uint32_t mask[kSR], lpre[kSR];
-  uint32_t kk[kSR][4];
-  uint32_t ncert = 0;  // random-k, direct lists: certain winners of this wavefront (uniform)
-  uint32_t cbits = 0;  // random-k, direct lists: bit 4r+q marks a certain winner (key below ulo)
-  uint32_t ntie = 0;   // top-k, sampled segments: elements equal to A of this wavefront (uniform)
-#pragma unroll
-  for (int r = 0; r < kSR; ++r) {
-    const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-    uint32_t mk = 0;
-    if constexpr (KIND == 0) {
-      // sampled segments: keys above A are stored, keys equal to A (the tie bin: exact zeros, say,
-      // which may be most of a segment) only counted; exact segments: the winner rule itself
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        kk[r][q] = mag_key(v[r][q]);
-        const bool in = (vm[r] >> q) & 1u;
-        if (in && (kk[r][q] > A || (mode != 0 && kk[r][q] == A && i0 + q < IA))) mk |= 1u << q;
-        if (mode == 0) ntie += (uint32_t)__popcll(__ballot(in && kk[r][q] == A));
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t u = uk[r][q];
-        if (((vm[r] >> q) & 1u) && (uint64_t)u < tau) {
-          mk |= 1u << q;
-          s_kk[(r * kStrNT + threadIdx.x) * 4 + q] = ~u;
-        }
-        if (((vm[r] >> q) & 1u) && u < ulo) cbits |= 1u << (4 * r + q);
-      }
-    }
-    mask[r] = mk;
-    uint32_t pre = 0, tot = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint64_t b = __ballot((mk >> q) & 1u);
-      pre += lanes_below(b);
-      tot += (uint32_t)__popcll(b);
-    }
-    lpre[r] = pre;
-    if (lane == 0) wt[r][wid] = tot;
-    if (direct) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) ncert += (uint32_t)__popcll(__ballot((cbits >> (4 * r + q)) & 1u));
-    }
-  }
-  if (direct) {
-    if (lane == 0) wc[wid] = ncert;
-    if (threadIdx.x == 0) s_und = 0;
-  }
-  if constexpr (KIND == 0) {
-    if (lane == 0) s_tie[wid] = ntie;
-  }
-  if constexpr (FUSED && KIND == 1) {
-    // random-k (as top-k segments with seg_zc, above): the residual is stored as +0 at every
-    // candidate; the emit kernel puts the value back at the few candidates that do not win (the
-    // window's losers, about 6 sqrt(k_l) + 32 of a segment), and the exact path puts them all back
-    // first.  Zeroing the winners afterwards instead wrote single words into lines long evicted
-    // from the caches: 1e9 elements at 10 %, 1.9 of the emission's 2.3 ms.
-#pragma unroll
-    for (int r = 0; r < kSR; ++r) {
-      const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-      float o[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) o[q] = ((mask[r] >> q) & 1u) ? 0.0f : v[r][q];
-      store4m(acc_out, i0, vm[r], o);
-    }
-  }
-  __syncthreads();
-  // the row's candidates go to its static slot, or, when there are more than it holds, to entries
-  // reserved in the overflow pool; a row that does not fit is dropped and its segment takes the
-  // exact path (the histogram still counts its candidates)
-  // (the wavefront totals are read once: the row's total, and each group's first position for
-  // this wavefront; the total and the slot are uniform, kept in scalar registers)
-  uint32_t tot = 0, rbs[kSR];
-#pragma unroll
-  for (int r = 0; r < kSR; ++r) {
-    uint32_t pre = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kStrW; ++w) {
-      const uint32_t c = wt[r][w];
-      pre += w < wid ? c : 0u;
-      all += c;
-    }
-    rbs[r] = tot + pre;
-    tot += all;
-  }
-  tot = __builtin_amdgcn_readfirstlane(tot);
-  if (tot > scap) {
-    if (threadIdx.x == 0) s_cb = pool_reserve(ws, row, tot);
-    __syncthreads();
-    cb = __builtin_amdgcn_readfirstlane(s_cb);
-  }
-  const bool dropped = cb == kDropped;
-  if (threadIdx.x == 0 && (T.L > 1 || tot > scap)) ws.coff[row] = cb;
-  if (dropped) {
-    if constexpr (KIND == 0) {
-      if (threadIdx.x == 0) atomicOr(&R[R_OVF], 1u);
-    }
-    if (FUSED && (KIND == 1 || zc)) {
-      // the candidates' values were stored as +0 above; without the candidates the exact path
-      // cannot restore them, so they are stored again now
-#pragma unroll
-      for (int r = 0; r < kSR; ++r) {
-        const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-        store4m(acc_out, i0, vm[r], v[r]);
-      }
-    }
-  }
-  uint32_t* cidx = ws.cand_idx + cb;
-  float* cval = ws.cand_val + cb;
-  uint32_t* ckey = ws.cand_key + cb;
-#pragma unroll
-  for (int r = 0; r < kSR; ++r) {
-    if (mask[r] && !dropped) {
-      const uint32_t i0 = tb + (uint32_t)(r * kStrNT + threadIdx.x) * 4u;
-      uint32_t pos = rbs[r] + lpre[r];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if ((mask[r] >> q) & 1u) {
-          uint32_t key;
-          if constexpr (KIND == 0) key = kk[r][q];
-          else key = s_kk[(r * kStrNT + threadIdx.x) * 4 + q];
-          cidx[pos] = i0 + q;
-          cval[pos] = v[r][q];
-          ckey[pos] = key;
-          ++pos;
-          if (direct && !((cbits >> (4 * r + q)) & 1u)) {
-            // random-k, direct lists: an undecided candidate ([ulo, tau)) joins the row's list as
-            // a (key', index) pair, at the row's pool entries in the pair array (fewer than its
-            // candidates)
-            const uint32_t p = atomicAdd(&s_und, 1u);
-            ws.pairs[(size_t)cb + p] = make_uint2(key, i0 + q);
-          }
-        }
-      }
-    }
-  }
-  const uint32_t base = tot;  // the row's candidates
-  if (threadIdx.x == 0) ws.counts[row] = base;
-  if (direct && threadIdx.x == 0) {
-    // random-k, direct lists: the row's certain winners (key below ulo)
-    uint32_t c = 0;
-#pragma unroll
-    for (int w = 0; w < kStrW; ++w) c += wc[w];
-    ws.rcnt[row] = c;
-  }
-  if constexpr (KIND == 0) {
-    if (mode == 0 && threadIdx.x == 0) {
-      // the ties are the histogram's bin 0
-      uint32_t t = 0;
-#pragma unroll
-      for (int w = 0; w < kStrW; ++w) t += s_tie[w];
-      ws.rtie[row] = t;
-      if (t) atomicAdd(&ws.hist[((size_t)l * kHCopies + (row % kHCopies)) * kHBins], t);
-    }
-    if (mode == 0 && base) {
-      uint32_t* gh = ws.hist + ((size_t)l * kHCopies + (row % kHCopies)) * kHBins;
-      if (base > kHistDirect) {  // many candidates: count them in LDS, then one atomic per used bin
-        for (int b = threadIdx.x; b < kHBins; b += kStrNT) s_hist[b] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kSR; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if ((mask[r] >> q) & 1u) atomicAdd(&s_hist[cand_bin(kk[r][q], A, sh)], 1u);
-        __syncthreads();
-        for (int b = threadIdx.x; b < kHBins; b += kStrNT) {
-          const uint32_t c = s_hist[b];
-          if (c) atomicAdd(&gh[b], c);
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < kSR; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if ((mask[r] >> q) & 1u) atomicAdd(&gh[cand_bin(kk[r][q], A, sh)], 1u);
-      }
-    }
-  }
+  if (lo == tb && hi == tb + kTile)
+    stream_row<KIND, GDT, FUSED, ZC, DIRECT, true>(T, g, src, acc_out, s0, s1, step, ws, S, row, l, o, tb, lo, hi, cb, scap);
+  else
+    stream_row<KIND, GDT, FUSED, ZC, DIRECT, false>(T, g, src, acc_out, s0, s1, step, ws, S, row, l, o, tb, lo, hi, cb, scap);
 }
 
 // Top-k, per segment: the histogram bin B holding the k_l-th best candidate and how many winners
@@ -1999,7 +1990,7 @@ __device__ __forceinline__ void collect_retry(const Tables& T, const WSel& ws, c
     const uint32_t oc = ws.counts[row];
     const uint32_t oco = row_entry(T, ws, row, oc, ws.coff[row]);
     if (oco != kDropped)
-      for (uint32_t j = lane; j < oc; j += 64) accw[ws.cand_idx[(size_t)oco + j]] = ws.cand_val[(size_t)oco + j];
+      for (uint32_t j = lane; j < oc; j += 64) accw[tb + ws.cand_loc[(size_t)oco + j]] = ws.cand_val[(size_t)oco + j];
     __threadfence();
   }
   // pass 1: how many (above A2, and equal)
@@ -2024,9 +2015,8 @@ __device__ __forceinline__ void collect_retry(const Tables& T, const WSel& ws, c
     return;
   }
   // pass 2: the candidates and the list
-  uint32_t* cidx = ws.cand_idx + cb;
+  uint16_t* cloc = ws.cand_loc + cb;
   float* cval = ws.cand_val + cb;
-  uint32_t* ckey = ws.cand_key + cb;
   uint32_t m = 0, na = 0;
   for (uint32_t i0 = lo; i0 < hi; i0 += 64) {
     const uint32_t i = i0 + lane;
@@ -2036,9 +2026,8 @@ __device__ __forceinline__ void collect_retry(const Tables& T, const WSel& ws, c
     const uint64_t bt = __ballot(take), bl = __ballot(lst);
     if (take) {
       const uint32_t pos = m + lanes_below(bt);
-      cidx[pos] = i;
+      cloc[pos] = (uint16_t)(i - tb);
       cval[pos] = v;
-      ckey[pos] = key;
     }
     m += (uint32_t)__popcll(bt);
     na += (uint32_t)__popcll(__ballot(cert));
@@ -2063,18 +2052,19 @@ __device__ __forceinline__ void collect_retry(const Tables& T, const WSel& ws, c
 
 constexpr uint32_t kCollectBuf = 512;  // listed candidates a wavefront of k_collect stages in LDS
 
-template <int KIND, uint32_t kCollectRows>
+template <uint32_t kCollectRows>
 __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
   __shared__ uint32_t s_lk[kNT / 64][kCollectBuf], s_li[kNT / 64][kCollectBuf];
   const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const uint32_t row0 = (blockIdx.x * (kNT / 64) + (threadIdx.x >> 6)) * kCollectRows;
   int ls[kCollectRows];
-  uint32_t cnts[kCollectRows], cofs[kCollectRows], k0[kCollectRows], i0[kCollectRows];
+  uint32_t cnts[kCollectRows], cofs[kCollectRows];
+  float v0[kCollectRows];
   // one segment: its record read once, in the first round trip (k_collect does not write it; read
   // per row, each row's fields waited for again after the previous row's list stores)
   uint32_t r_skip = 0, r_retry = 0, r_A = 0, r_sh = 0, r_B = 0;
-  if (KIND == 0 && T.L == 1) {
+  if (T.L == 1) {
     const uint32_t* R0 = res_of(ws, 0);
     r_skip = R0[R_SLOW] | R0[R_MODE];
     r_retry = R0[R_RETRY];
@@ -2088,13 +2078,10 @@ __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
     ls[r] = T.L == 1 ? 0 : T.row_seg[row];  // one segment: no load before the segment's record
     cnts[r] = ws.counts[row];
     cofs[r] = ws.coff[row];
-    // one segment: the first 64 keys and indices from the row's static slot, in the same round
-    // trip (used if the row's candidates are there; past the count: unused, and not loaded past
-    // the slot)
-    const uint32_t cap0 = min(ws.S, (uint32_t)T.d - row * kTile);
-    const bool in0 = T.L == 1 && lane < cap0;
-    k0[r] = in0 ? ws.cand_key[(size_t)row * ws.S + lane] : 0u;
-    i0[r] = in0 ? ws.cand_idx[(size_t)row * ws.S + lane] : 0u;
+    // one segment: the first values of the row's static slot, in the same round trip (used if the
+    // row's candidates are there; past the count: unused, and not loaded past the slot)
+    const uint32_t cap0 = T.L == 1 ? min(ws.S, (uint32_t)T.d - row * kTile) : 0u;
+    v0[r] = lane < cap0 ? ws.cand_val[(size_t)row * ws.S + lane] : 0.0f;
   }
 #pragma unroll
   for (uint32_t r = 0; r < kCollectRows; ++r) {
@@ -2102,40 +2089,27 @@ __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
     if (row >= (uint32_t)T.nrows) break;
     const int l = ls[r];
     uint32_t* R = res_of(ws, l);
-    uint32_t A = 0, sh = 0, B = 0, ulo = 0;
-    if constexpr (KIND == 0) {
-      const bool one = T.L == 1;
-      if (one ? r_skip != 0 : (R[R_SLOW] || R[R_MODE])) continue;
-      if (one ? r_retry != 0 : R[R_RETRY] != 0) {
-        collect_retry(T, ws, BT, row, l, R);
-        continue;
-      }
-      A = one ? r_A : R[R_A];
-      sh = one ? r_sh : R[R_SH];
-      B = one ? r_B : R[R_B];
-    } else {
-      ulo = T.seg_ulo[l];
+    const bool one = T.L == 1;
+    if (one ? r_skip != 0 : (R[R_SLOW] || R[R_MODE])) continue;
+    if (one ? r_retry != 0 : R[R_RETRY] != 0) {
+      collect_retry(T, ws, BT, row, l, R);
+      continue;
     }
+    const uint32_t A = one ? r_A : R[R_A], sh = one ? r_sh : R[R_SH], B = one ? r_B : R[R_B];
     const uint32_t co = row_entry(T, ws, row, cnts[r], cofs[r]);
     if (co == kDropped) continue;  // the segment takes the exact path
-    // class: 2 = certain winner, 1 = undecided (listed), 0 = loses
-    auto cls = [&](uint32_t k) -> uint32_t {
-      if constexpr (KIND == 0) {
-        const uint32_t b = cand_bin(k, A, sh);
-        return b > B ? 2u : (b == B ? 1u : 0u);
-      } else {
-        return ~k < ulo ? 2u : 1u;
-      }
-    };
-    // tie bin (the threshold bin is the key A alone, whose elements the pass only counted): every
-    // stored candidate is a certain winner and nothing is listed
-    const bool tie_bin = KIND == 0 && B == 0;
+    // keys from k2 on (the first of bin B + 1) are certain winners, those from k1 on (bin B's first)
+    // undecided and listed.  Tie bin (B = 0, the key A alone, whose elements the pass only counted):
+    // every stored candidate is a certain winner and nothing is listed
+    const uint32_t k2 = B + 1u < (uint32_t)kHBins ? A + 1u + (B << sh) : 0xFFFFFFFFu;
+    const uint32_t k1 = B ? A + 1u + ((B - 1u) << sh) : k2;
     const uint32_t cnt = cnts[r];
-    const uint32_t* ck = ws.cand_key + co;
-    const uint32_t* ci = ws.cand_idx + co;
-    const bool k0_ok = T.L == 1 && co == row * ws.S;
+    const float* cv = ws.cand_val + co;
+    const uint16_t* ci = ws.cand_loc + co;
+    const bool v0_ok = one && co == row * ws.S;
     const uint32_t r0 = (uint32_t)T.seg_cbase[l], c = (row - r0) % kSubLists, lq = T.seg_lq[l];
     const size_t sb = sublist_base(T, l, c);
+    const uint32_t tb = row_tile(T, row);
     // The row's listed candidates are staged in the wavefront's LDS buffer and written out with
     // one reservation of list space per row (or per full buffer).  An atomic per chunk of 64
     // candidates, each waited for, on the 16 sub-list counters took 92-141 us to collect BERT flat
@@ -2154,26 +2128,92 @@ __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
       }
       nb = 0;
     };
-    uint32_t kc = k0_ok ? k0[r] : (lane < cnt ? ck[lane] : 0u);
+    float vc = v0_ok ? v0[r] : (lane < cnt ? cv[lane] : 0.0f);
+#pragma unroll 1
     for (uint32_t j0 = 0; j0 < cnt; j0 += 64) {
-      const uint32_t j = j0 + lane;
-      const uint32_t k = kc;
-      if (j0 + 64 < cnt) kc = j + 64 < cnt ? ck[j + 64] : 0u;  // the next chunk's keys, in flight
-      const uint32_t cl = j < cnt ? (tie_bin ? 2u : cls(k)) : 0u;
-      na += (uint32_t)__popcll(__ballot(cl == 2u));
-      const uint64_t bu = __ballot(cl == 1u);
+      const uint32_t left = cnt - j0, k = mag_key(vc);
+      if (left > 64u) vc = lane + 64u < left ? cv[j0 + 64u + lane] : 0.0f;  // the next chunk's values, in flight
+      const uint64_t there = left >= 64u ? ~0ull : (1ull << left) - 1ull;
+      const uint64_t b2 = __ballot(k >= k2) & there, bu = __ballot(k >= k1) & there & ~b2;
+      na += (uint32_t)__popcll(b2);
       const uint32_t nu = (uint32_t)__popcll(bu);
       if (nu == 0) continue;
       if (nb + nu > kCollectBuf) flush();
-      if (cl == 1u) {
+      if (__builtin_amdgcn_inverse_ballot_w64(bu)) {
         const uint32_t x = nb + lanes_below(bu);
         s_lk[wv][x] = k;
-        s_li[wv][x] = k0_ok && j0 == 0 ? i0[r] : ci[j];
+        s_li[wv][x] = tb + ci[j0 + lane];
       }
       nb += nu;
     }
     if (nb) flush();
     if (lane == 0) ws.rcnt[row] = na;
+  }
+}
+
+// Random-k without direct lists, per row: the undecided candidates ([ulo, tau)) go to the segment's
+// sub-lists, the certain winners are added to the segment's counters.  A wavefront looks at
+// kCollectRk rows' counts and reads the candidates of those that hold an undecided one only (1e9
+// elements at 1 %: one row in seven; every candidate's key read and tested took 65 us).
+constexpr uint32_t kCollectRk = 64;  // a lane each
+constexpr uint32_t kCollectWide = 1024;  // segments of at least this many rows: a wavefront reserves list space once
+__global__ __launch_bounds__(kNT) void k_collect_randk(Tables T, WSel ws0, Batch BT) {
+  const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t row0 = (blockIdx.x * (kNT / 64) + (threadIdx.x >> 6)) * kCollectRk;
+  if (row0 >= (uint32_t)T.nrows) return;
+  const uint32_t row = min(row0 + lane, (uint32_t)T.nrows - 1u);
+  const bool has = lane < kCollectRk && row0 + lane < (uint32_t)T.nrows;
+  int l = 0;
+  uint32_t cnt = 0, cert = 0, co = kDropped, tb = 0, sub = 0;
+  if (has) {
+    l = T.L == 1 ? 0 : T.row_seg[row];
+    cnt = ws.counts[row];
+    cert = ws.rcnt[row];
+    tb = row_tile(T, row);
+    co = row_entry(T, ws, row, cnt, ws.coff[row]);
+    sub = (row - (uint32_t)T.seg_cbase[l]) % kSubLists;
+    if (co == kDropped) atomicOr(&res_of(ws, l)[R_OVF], 1u);
+  }
+  const int l0 = __builtin_amdgcn_readfirstlane(l);  // (the first row: lane 0 has one)
+  if (__ballot(has && l != l0) == 0) {  // rows of one segment: one addition
+    const uint32_t s = wave_incl_scan(cert);
+    if (lane == 63 && s) atomicAdd(scnt_of(ws, l0, (row0 / kCollectRk) % kSubLists), s);
+  } else if (has && cert) {
+    atomicAdd(scnt_of(ws, l, sub), cert);
+  }
+  const bool list = has && co != kDropped && cnt > cert;
+  uint32_t at = 0;
+  // (the 16 counters take one atomic at a time, about 15 ns each)
+  if (__ballot(has && l != l0) == 0 && (uint32_t)(T.seg_cbase[l0 + 1] - T.seg_cbase[l0]) >= kCollectWide) {
+    const uint32_t und = list ? cnt - cert : 0u, inc = wave_incl_scan(und);
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    sub = (row0 / kCollectRk) % kSubLists;
+    if (all && lane == 0) at = atomicAdd(lcnt_of(ws, l0, sub), all);
+    at = (uint32_t)__builtin_amdgcn_readlane((int)at, 0) + inc - und;
+  } else if (list) {
+    at = atomicAdd(lcnt_of(ws, l, sub), cnt - cert);
+  }
+  uint64_t todo = __ballot(list);
+  while (todo) {
+    const int j = __ffsll((long long)todo) - 1;
+    todo &= todo - 1;
+    const int rl = __builtin_amdgcn_readlane(l, j);
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)cnt, j), c0 = (uint32_t)__builtin_amdgcn_readlane((int)co, j);
+    const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)tb, j), lq = T.seg_lq[rl];
+    const size_t sb = sublist_base(T, rl, (uint32_t)__builtin_amdgcn_readlane((int)sub, j));
+    uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)at, j);
+    for (uint32_t f0 = 0; f0 < n; f0 += 64) {
+      const uint32_t f = f0 + lane;
+      const uint32_t x = f < n ? ws.cand_loc[(size_t)c0 + f] : kCertain;
+      const uint64_t b = __ballot(!(x & kCertain));
+      const uint32_t t = p + lanes_below(b);
+      if (!(x & kCertain) && t < lq) {  // a full sub-list is seen by k_select (its count exceeds lq)
+        ws.list_key[sb + t] = ws.cand_key[(size_t)c0 + f];
+        ws.list_idx[sb + t] = t0 + x;
+      }
+      p += (uint32_t)__popcll(b);
+    }
   }
 }
 
@@ -2317,9 +2357,10 @@ __device__ __forceinline__ void list_threshold(const K& key, const K& idx, uint3
 // Per segment: the exact threshold among the listed candidates, then every row's message offset;
 // or the exact whole-segment path when the candidates cannot hold the answer.  Independent loads
 // are issued together (record, sub-list sizes, the rows' counts) to keep the chain of dependent
-// memory round trips short.  BIG (layouts with a very large k_l): only the threshold; the rows'
-// winners are then counted by k_rowcount and scanned by k_rowscan, both spread over many
-// workgroups, instead of one workgroup adding the list's winners to their rows.
+// memory round trips short.  BIG (layouts with a very large k_l or very many rows): the threshold, and
+// the list's winners added to their rows' counts with global atomics (the listed candidates are few
+// beside the winners, so that counting every row's winners again, 22 us on BERT flat at 10 % and 55 us
+// on 1e9 elements at 1 %, is not needed); k_rowsum turns the counts into offsets over many workgroups.
 template <int KIND, bool BIG>
 __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t* out_idx, float* out_val,
                                                    uint32_t step, Batch BT) {
@@ -2334,7 +2375,7 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
   __shared__ uint32_t lds[3 * kSelNT / 64];
   __shared__ uint32_t s_key[kListLds];
   __shared__ uint32_t s_idx[kListLds];
-  __shared__ uint32_t s_add[kRowsLds];
+  __shared__ uint32_t s_add[BIG ? 1 : kRowsLds];
   __shared__ uint64_t s_g[kRankList];
   const int l = blockIdx.x;
   uint32_t* R = res_of(ws, l);
@@ -2384,10 +2425,7 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
       }
     }
   }
-  // random-k on a layout with very many rows needs only the totals: the rows are summed with
-  // coalesced strided loads there, not in per-thread runs (one workgroup reading 244,141 rows in
-  // runs of 238 per thread took 0.44 ms at 1e9 elements)
-  const bool strided = KIND == 1 && !direct && BIG;
+  const bool counted = KIND == 1 && !direct;  // (the pass counted the certain winners by segment)
   // random-k: the rows' first pool entries (one segment: the static slot, r * S, unless the row
   // holds more candidates than it, so only those rows' entries are loaded)
   const uint32_t* ro = ws.coff + r0;
@@ -2398,11 +2436,11 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
   uint32_t cr[kPer], cn[kPer], co[kPer];
 #pragma unroll
   for (uint32_t x = 0; x < kPer; ++x) {
-    cr[x] = !strided && a + x < b ? rc[a + x] : 0u;
-    cn[x] = !strided && a + x < b ? cc[a + x] : 0u;
-    co[x] = KIND == 1 && T.L > 1 && !strided && a + x < b ? ro[a + x] : 0u;
+    cr[x] = !(counted && BIG) && a + x < b ? rc[a + x] : 0u;
+    cn[x] = !counted && a + x < b ? cc[a + x] : 0u;
+    co[x] = KIND == 1 && T.L > 1 && !counted && a + x < b ? ro[a + x] : 0u;
   }
-  if (KIND == 1 && T.L == 1 && !strided) {
+  if (KIND == 1 && T.L == 1 && !counted) {
 #pragma unroll
     for (uint32_t x = 0; x < kPer; ++x)
       if (a + x < b) co[x] = first_entry(a + x, cn[x]);
@@ -2411,28 +2449,19 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
     // random-k: the certain winners S (keys below ulo) and the candidates N decide whether the
     // window [ulo, tau) holds the k_l-th smallest key (also counted: rows whose candidates did not
     // fit the workspace)
-    uint32_t sv[3] = {0u, 0u, 0u};
-    if (strided) {
-      constexpr uint32_t kU = 8;
-      for (uint32_t x0 = threadIdx.x; x0 < nr; x0 += kU * kSelNT) {
-        uint32_t ra[kU], ca[kU], oa[kU];
+    uint32_t S, N, dropped;
+    if (counted) {
+      uint32_t m = 0;
+      S = 0;
 #pragma unroll
-        for (uint32_t u = 0; u < kU; ++u) {
-          const uint32_t x = x0 + u * kSelNT;
-          ra[u] = x < nr ? rc[x] : 0u;
-          ca[u] = x < nr ? cc[x] : 0u;
-          oa[u] = x < nr && T.L > 1 ? ro[x] : 0u;
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < kU; ++u) {
-          const uint32_t x = x0 + u * kSelNT;
-          if (T.L == 1 && x < nr) oa[u] = first_entry(x, ca[u]);
-          sv[0] += ra[u];
-          sv[1] += ca[u];
-          sv[2] += oa[u] == kDropped ? 1u : 0u;
-        }
+      for (int c = 0; c < kSubLists; ++c) {
+        S += *scnt_of(ws, l, (uint32_t)c);
+        m += lc[c];
       }
+      N = S + m;
+      dropped = R[R_OVF];
     } else {
+      uint32_t sv[3] = {0u, 0u, 0u};
 #pragma unroll
       for (uint32_t x = 0; x < kPer; ++x) {
         sv[0] += cr[x];
@@ -2445,16 +2474,18 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
         sv[1] += c;
         sv[2] += (T.L == 1 ? first_entry(x, c) : ro[x]) == kDropped ? 1u : 0u;
       }
+      uint32_t ex[3], tot[3];
+      block_excl_scan_n<kSelNT, 3>(sv, lds, ex, tot);
+      S = tot[0];
+      N = tot[1];
+      dropped = tot[2];
+      exU = ex[1] - ex[0];
     }
-    uint32_t ex[3], tot[3];
-    block_excl_scan_n<kSelNT, 3>(sv, lds, ex, tot);
-    const uint32_t S = tot[0], N = tot[1];
     // direct lists: the rows' undecided candidates (counts - certain) must fit the LDS list;
-    // collected lists: every sub-list its region
-    slow = S > kl || N < kl || tot[2] != 0 || (direct ? N - S > kListLds : lfull);
+    // sub-lists: every one its region
+    slow = S > kl || N < kl || dropped != 0 || (direct ? N - S > kListLds : lfull);
     need = kl - S;
     mU = N - S;
-    exU = ex[1] - ex[0];
     if (threadIdx.x == 0) {
       R[R_SLOW] = slow ? 1u : 0u;
       if (slow) atomicOr(ws.diag, kDiagSlowPath);
@@ -2466,10 +2497,11 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
   auto restore_candidates = [&]() {
     if (!e_zero || (KIND == 0 && !T.seg_zc[l])) return;
     for (uint32_t x = a; x < b; ++x) {
-      const uint32_t cnt = cc[x];
+      const uint32_t cnt = cc[x], tb = row_tile(T, r0 + x);
       const uint32_t sl = T.L == 1 ? first_entry(x, cnt) : ro[x];
       if (sl == kDropped) continue;
-      for (uint32_t j = 0; j < cnt; ++j) e_zero[ws.cand_idx[(size_t)sl + j]] = ws.cand_val[(size_t)sl + j];
+      for (uint32_t j = 0; j < cnt; ++j)
+        e_zero[tb + (ws.cand_loc[(size_t)sl + j] & (kTile - 1u))] = ws.cand_val[(size_t)sl + j];
     }
     __threadfence();
     __syncthreads();
@@ -2481,6 +2513,7 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
   }
   const bool rows_lds = nr <= kRowsLds;
   bool tie = false;
+  bool done = KIND == 1;  // many rows: the rows' winner counts are complete
   if constexpr (KIND == 0) tie = listed && (R[R_B] == 0 || retry_ties);
   if (tie) {
     // The threshold bin is the key A alone, whose elements the streaming pass counted per row but
@@ -2567,10 +2600,10 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
     if (e_zero && T.seg_zc[l] && !R[R_RETRY]) {
       // the pass stored +0 at this row's candidates: back to acc before its elements are searched
       // (+0 has the key of a tie at A = 0)
-      const uint32_t row = r0 + s_row, oc = ws.rtie[row];
+      const uint32_t row = r0 + s_row, oc = ws.rtie[row], tb = row_tile(T, row);
       const uint32_t co = row_entry(T, ws, row, oc, ws.coff[row]);
       if (co != kDropped)
-        for (uint32_t j = threadIdx.x; j < oc; j += kSelNT) e_zero[ws.cand_idx[(size_t)co + j]] = ws.cand_val[(size_t)co + j];
+        for (uint32_t j = threadIdx.x; j < oc; j += kSelNT) e_zero[tb + ws.cand_loc[(size_t)co + j]] = ws.cand_val[(size_t)co + j];
       __threadfence();
       __syncthreads();
     }
@@ -2651,7 +2684,7 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
         }
       }
     }
-    if (rows_lds)
+    if (!BIG && rows_lds)
       for (uint32_t x = threadIdx.x; x < nr; x += kSelNT) s_add[x] = 0;
     __syncthreads();
     // need == 0 (random-k only): the certain winners, keys below ulo, are all the winners
@@ -2675,13 +2708,15 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
       } else {
         list_threshold(lk, li, m, need, hist, lds, s_g, Tk, IT, defer);
       }
-      // the list's winners join their rows' counts
+      // the list's winners join their rows' counts (many rows, top-k: a list that fits LDS, else the
+      // rows are counted again by k_rowcount)
       const uint32_t c0 = o / kTile;
-      for (uint32_t j = threadIdx.x; j < (BIG ? 0u : m); j += kSelNT) {
+      if constexpr (BIG) done = IT != kTieRows && (KIND == 1 || in_lds);
+      for (uint32_t j = threadIdx.x; j < (!BIG || done ? m : 0u); j += kSelNT) {
         const uint32_t k = in_lds ? s_key[j] : lk[j];
         const uint32_t i = in_lds ? s_idx[j] : li[j];
         if (k > Tk || (k == Tk && i < IT)) {
-          if (rows_lds) atomicAdd(&s_add[i / kTile - c0], 1u);
+          if (!BIG && rows_lds) atomicAdd(&s_add[i / kTile - c0], 1u);
           else atomicAdd(&ws.rcnt[r0 + (i / kTile - c0)], 1u);
         }
       }
@@ -2700,7 +2735,10 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
     }
     __syncthreads();
   }
-  if constexpr (BIG) return;
+  if constexpr (BIG) {
+    if (KIND == 0 && threadIdx.x == 0) R[R_DONE] = done ? 1u : 0u;
+    return;
+  }
   // row offsets: exclusive scan of the rows' winner counts (mode 1: every candidate wins)
   const uint32_t* cnt = listed ? rc : cc;
   const bool add = listed && rows_lds && !tie;
@@ -2727,12 +2765,10 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
   if (threadIdx.x == 0 && tot != kl) atomicOr(ws.diag, kDiagCount);
 }
 
-// Large layouts, per row: how many of the row's candidates win (all of them in mode 1).  One
-// wavefront per row, kRowcountU chunks of 64 candidates loaded together, counts by ballots (one
-// 256-thread workgroup per row, with a workgroup scan, took 180 us over the 244,141 rows of 1e9
-// elements).
+// Top-k, many rows, per row of a segment whose list did not fit k_select's LDS (or whose ties or
+// retry change the rows' counts): how many of the row's candidates win.  One wavefront per row,
+// kRowcountU chunks of 64 candidates loaded together, counts by ballots.
 constexpr uint32_t kRowcountU = 4;
-template <int KIND>
 __global__ __launch_bounds__(kNT) void k_rowcount(Tables T, WSel ws0, Batch BT) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
   const uint32_t lane = threadIdx.x & 63;
@@ -2740,38 +2776,33 @@ __global__ __launch_bounds__(kNT) void k_rowcount(Tables T, WSel ws0, Batch BT) 
   if (row >= (uint32_t)T.nrows) return;
   const int l = T.L == 1 ? 0 : T.row_seg[row];
   const uint32_t* R = res_of(ws, l);
-  if (R[R_SLOW]) return;
+  if (R[R_SLOW] || R[R_MODE] || R[R_DONE]) return;
   const uint32_t cw = ws.counts[row], cnt = cw & ~kAccRow;
   // a row emitted from acc (winning ties): k_select wrote its winner count (its stored candidates,
   // which all win, and the ties it takes)
-  if (KIND == 0 && (cw & kAccRow)) return;
-  const uint32_t co = row_entry(T, ws, row, cnt, ws.coff[row]);
+  if (cw & kAccRow) return;
+  const uint32_t co = row_entry(T, ws, row, cnt, ws.coff[row]), tb = row_tile(T, row);
   uint32_t won = 0, tie = 0;
-  bool defer = false;  // ties at T resolved by k_rowscan: count them apart
-  if (KIND == 1 || R[R_MODE] == 0) {
-    const uint32_t Tk = R[R_T], IT = R[R_IT];
-    defer = KIND == 0 && IT == kTieRows;
-    const uint32_t* ck = ws.cand_key + co;
-    const uint32_t* ci = ws.cand_idx + co;
-    for (uint32_t j0 = 0; j0 < cnt; j0 += 64u * kRowcountU) {
-      uint32_t k[kRowcountU];
+  const uint32_t Tk = R[R_T], IT = R[R_IT];
+  const bool defer = IT == kTieRows;  // ties at T resolved by k_rowtie: count them apart
+  const float* cv = ws.cand_val + co;
+  const uint16_t* ci = ws.cand_loc + co;
+  for (uint32_t j0 = 0; j0 < cnt; j0 += 64u * kRowcountU) {
+    float v[kRowcountU];
 #pragma unroll
-      for (uint32_t u = 0; u < kRowcountU; ++u) {
-        const uint32_t j = j0 + 64u * u + lane;
-        k[u] = j < cnt ? ck[j] : 0u;
-      }
-#pragma unroll
-      for (uint32_t u = 0; u < kRowcountU; ++u) {
-        const uint32_t j = j0 + 64u * u + lane;
-        const bool in = j < cnt;
-        // (the index only for a key equal to the threshold key)
-        const bool w = in && (k[u] > Tk || (!defer && k[u] == Tk && ci[j] < IT));
-        won += (uint32_t)__popcll(__ballot(w));
-        tie += (uint32_t)__popcll(__ballot(in && defer && k[u] == Tk));
-      }
+    for (uint32_t u = 0; u < kRowcountU; ++u) {
+      const uint32_t j = j0 + 64u * u + lane;
+      v[u] = j < cnt ? cv[j] : 0.0f;
     }
-  } else {
-    won = cnt;
+#pragma unroll
+    for (uint32_t u = 0; u < kRowcountU; ++u) {
+      const uint32_t j = j0 + 64u * u + lane, k = mag_key(v[u]);
+      const bool in = j < cnt;
+      // (the index only for a key equal to the threshold key)
+      const bool w = in && (k > Tk || (!defer && k == Tk && tb + ci[j] < IT));
+      won += (uint32_t)__popcll(__ballot(w));
+      tie += (uint32_t)__popcll(__ballot(in && defer && k == Tk));
+    }
   }
   if (lane == 0) {
     ws.rcnt[row] = won;
@@ -2779,118 +2810,133 @@ __global__ __launch_bounds__(kNT) void k_rowcount(Tables T, WSel ws0, Batch BT) 
   }
 }
 
-// Large layouts, per segment: message offset of every row (exclusive scan of the winner counts),
-// in tiles of kSelNT * 8 rows: coalesced loads into LDS, eight consecutive rows per thread, a
-// workgroup scan, coalesced stores.  A top-k segment whose threshold key T is shared by more
-// candidates than win (R_IT = kTieRows) first scans the rows' counts of keys equal to T the same
-// way: the row where the R_NEED-th falls, then that tie inside the row's candidates (stored in
-// index order) give R_IT, and the rows before it add all their ties to their winners, the row
-// itself the ties up to that one.
-__global__ __launch_bounds__(kSelNT) void k_rowscan(Tables T, WSel ws0, Batch BT) {
+// Magnitude keys of a row's stored candidates.
+struct CandKeys {
+  const float* v;
+  __device__ __forceinline__ uint32_t operator[](uint32_t f) const { return mag_key(v[f]); }
+};
+
+// Top-k, many rows, per segment whose threshold key T is shared by more candidates than win (R_IT =
+// kTieRows): a scan of the rows' counts of keys equal to T (tiles of kSelNT * 8 rows: coalesced loads
+// into LDS, eight consecutive rows per thread, a workgroup scan) finds the row where the R_NEED-th
+// falls, then that tie inside the row's candidates (stored in index order) gives R_IT, and the rows
+// before it add all their ties to their winners, the row itself the ties up to that one.
+__global__ __launch_bounds__(kSelNT) void k_rowtie(Tables T, WSel ws0, Batch BT) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
   constexpr uint32_t kU = 8, kTl = kSelNT * kU;
   __shared__ uint32_t lds[2 * kSelNT / 64];
   __shared__ uint32_t s_c[kTl + kTl / 32];
+  __shared__ uint32_t s_row, s_rank;
   auto pad = [](uint32_t i) { return i + (i >> 5); };
   const int l = blockIdx.x;
   const uint32_t* R = res_of(ws, l);
-  if (R[R_SLOW]) return;
+  if (R[R_SLOW] || R[R_MODE] || R[R_IT] != kTieRows) return;
   const uint32_t r0 = (uint32_t)T.seg_cbase[l], nr = (uint32_t)T.seg_cbase[l + 1] - r0;
-  const uint32_t* cnt = ws.rcnt + r0;
+  uint32_t* cnt = ws.rcnt + r0;
   const uint32_t* rt = ws.rtie + r0;
-  uint32_t* roff = ws.roff + r0;
-  const bool defer = R[R_IT] == kTieRows;  // uniform
-  __shared__ uint32_t s_row, s_rank;
-  if (defer) {
-    const uint32_t need = R[R_NEED];
-    if (threadIdx.x == 0) {
-      s_row = nr;
-      s_rank = 0;
-    }
-    uint32_t before = 0;  // ties in earlier tiles
-    for (uint32_t t0 = 0; t0 < nr; t0 += kTl) {
-      uint32_t v[kU];
-#pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) {
-        const uint32_t x = t0 + u * kSelNT + threadIdx.x;
-        v[u] = x < nr ? rt[x] : 0u;
-      }
-#pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) s_c[pad(u * kSelNT + threadIdx.x)] = v[u];
-      __syncthreads();
-      uint32_t sum = 0;
-#pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) {
-        v[u] = s_c[pad(threadIdx.x * kU + u)];
-        sum += v[u];
-      }
-      uint32_t tot;
-      uint32_t run = before + block_excl_scan<kSelNT>(sum, lds, tot);
-#pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) {
-        if (run < need && need <= run + v[u]) {
-          s_row = t0 + threadIdx.x * kU + u;
-          s_rank = need - run;
-        }
-        run += v[u];
-      }
-      before += tot;
-      __syncthreads();
-    }
-    __syncthreads();
-    // the s_rank-th key equal to T among the row's candidates (index order): the last winner
-    const uint32_t sr = s_row;
-    if (sr < nr) {
-      const uint32_t row = r0 + sr, c = ws.counts[row];
-      const uint32_t co = row_entry(T, ws, row, c, ws.coff[row]);
-      const uint32_t p = block_nth_equal(ws.cand_key + co, c, R[R_T], s_rank, lds);
-      if (threadIdx.x == 0) res_of(ws, l)[R_IT] = ws.cand_idx[co + p] + 1u;
-    }
+  const uint32_t need = R[R_NEED], Tk = R[R_T];
+  if (threadIdx.x == 0) {
+    s_row = nr;
+    s_rank = 0;
   }
-  uint32_t carry = (uint32_t)T.seg_P[l], total = 0;
-  // the offsets pass, with the ties of the rows up to s_row added to their winners or without
-  auto offsets = [&](auto with_ties) {
-    constexpr bool TI = decltype(with_ties)::value;
-    const uint32_t srow = TI ? s_row : 0u, srank = TI ? s_rank : 0u;
-    for (uint32_t t0 = 0; t0 < nr; t0 += kTl) {
-      uint32_t v[kU];
+  uint32_t before = 0;  // ties in earlier tiles
+  for (uint32_t t0 = 0; t0 < nr; t0 += kTl) {
+    uint32_t v[kU];
 #pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) {
-        const uint32_t x = t0 + u * kSelNT + threadIdx.x;
-        uint32_t tk = 0;  // ties at T: all of a row before srow win, srank of row srow
-        if constexpr (TI) tk = x < srow ? rt[x] : (x == srow ? srank : 0u);
-        v[u] = x < nr ? cnt[x] + tk : 0u;
-      }
-#pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) s_c[pad(u * kSelNT + threadIdx.x)] = v[u];
-      __syncthreads();
-      uint32_t sum = 0;
-#pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) {
-        v[u] = s_c[pad(threadIdx.x * kU + u)];
-        sum += v[u];
-      }
-      uint32_t tot;
-      uint32_t run = carry + block_excl_scan<kSelNT>(sum, lds, tot);
-#pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) {
-        s_c[pad(threadIdx.x * kU + u)] = run;
-        run += v[u];
-      }
-      __syncthreads();
-#pragma unroll
-      for (uint32_t u = 0; u < kU; ++u) {
-        const uint32_t x = t0 + u * kSelNT + threadIdx.x;
-        if (x < nr) roff[x] = s_c[pad(u * kSelNT + threadIdx.x)];
-      }
-      __syncthreads();
-      carry += tot;
-      total += tot;
+    for (uint32_t u = 0; u < kU; ++u) {
+      const uint32_t x = t0 + u * kSelNT + threadIdx.x;
+      v[u] = x < nr ? rt[x] : 0u;
     }
-  };
-  if (defer) offsets(std::true_type{});
-  else offsets(std::false_type{});
-  if (threadIdx.x == 0 && total != (uint32_t)T.seg_k[l]) atomicOr(ws.diag, kDiagCount);
+#pragma unroll
+    for (uint32_t u = 0; u < kU; ++u) s_c[pad(u * kSelNT + threadIdx.x)] = v[u];
+    __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < kU; ++u) {
+      v[u] = s_c[pad(threadIdx.x * kU + u)];
+      sum += v[u];
+    }
+    uint32_t tot;
+    uint32_t run = before + block_excl_scan<kSelNT>(sum, lds, tot);
+#pragma unroll
+    for (uint32_t u = 0; u < kU; ++u) {
+      if (run < need && need <= run + v[u]) {
+        s_row = t0 + threadIdx.x * kU + u;
+        s_rank = need - run;
+      }
+      run += v[u];
+    }
+    before += tot;
+    __syncthreads();
+  }
+  __syncthreads();
+  // the s_rank-th key equal to T among the row's candidates (index order): the last winner
+  const uint32_t sr = s_row, srank = s_rank;
+  if (sr < nr) {
+    const uint32_t row = r0 + sr, c = ws.counts[row];
+    const uint32_t co = row_entry(T, ws, row, c, ws.coff[row]);
+    const uint32_t p = block_nth_equal(CandKeys{ws.cand_val + co}, c, Tk, srank, lds);
+    if (threadIdx.x == 0) res_of(ws, l)[R_IT] = row_tile(T, row) + ws.cand_loc[(size_t)co + p] + 1u;
+  }
+  for (uint32_t x = threadIdx.x; x < nr && x <= sr; x += kSelNT) cnt[x] += x < sr ? rt[x] : srank;
+}
+
+// Many rows: the winners of each of at most kRowBlocks blocks of `rows` consecutive rows (a multiple of
+// kRowsumT; one workgroup each), and every row's winners before it in its block.  A segment's rows
+// hold k_l winners in all, so a row's message position is the winners of all the rows before it,
+// whichever segments they belong to.  (One workgroup walking all rows took 63 us over the 244,141
+// rows of 1e9 elements.)
+constexpr uint32_t kRowsumT = kNT * 8u;
+template <int KIND>
+__global__ __launch_bounds__(kNT) void k_rowsum(Tables T, WSel ws0, Batch BT, uint32_t rows) {
+  const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
+  __shared__ uint32_t lds[kNT / 64];
+  const uint32_t b0 = blockIdx.x * rows, b1 = min((uint32_t)T.nrows, b0 + rows);
+  uint32_t run = 0;
+  for (uint32_t t0 = b0; t0 < b1; t0 += kRowsumT) {
+    const uint32_t x0 = t0 + threadIdx.x * 8u;
+    uint32_t c[8], sum = 0;
+    if (x0 + 8u <= b1) {  // rows start at multiples of eight
+      const uint4 p = *reinterpret_cast<const uint4*>(ws.rcnt + x0), q = *reinterpret_cast<const uint4*>(ws.rcnt + x0 + 4);
+      c[0] = p.x; c[1] = p.y; c[2] = p.z; c[3] = p.w;
+      c[4] = q.x; c[5] = q.y; c[6] = q.z; c[7] = q.w;
+    } else {
+#pragma unroll
+      for (uint32_t u = 0; u < 8u; ++u) c[u] = x0 + u < b1 ? ws.rcnt[x0 + u] : 0u;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 8u; ++u) {
+      const uint32_t x = x0 + u;
+      if (x < b1) {
+        const int l = T.L == 1 ? 0 : T.row_seg[x];
+        const uint32_t* R = res_of(ws, l);
+        // the exact path wrote its segment's message: its first row stands for all
+        if (R[R_SLOW]) c[u] = x == (uint32_t)T.seg_cbase[l] ? (uint32_t)T.seg_k[l] : 0u;
+        else if (KIND == 0 && R[R_MODE]) c[u] = ws.counts[x];  // every candidate wins
+      }
+      sum += c[u];
+    }
+    uint32_t tot;
+    uint32_t at = run + block_excl_scan<kNT>(sum, lds, tot);
+#pragma unroll
+    for (uint32_t u = 0; u < 8u; ++u) {
+      if (x0 + u < b1) ws.roff[x0 + u] = at;
+      at += c[u];
+    }
+    run += tot;
+  }
+  if (threadIdx.x == 0) ws.bsum[blockIdx.x] = run;
+}
+
+// The sum of the first b blocks' winners (uniform b; one wavefront).
+__device__ __forceinline__ uint32_t rows_before(const WSel& ws, uint32_t b) {
+  uint32_t s = 0;
+#pragma unroll
+  for (uint32_t u = 0; u < kRowBlocks / 64u; ++u) {
+    const uint32_t j = u * 64u + (threadIdx.x & 63u);
+    if (j < b) s += ws.bsum[j];
+  }
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(s), 63);
 }
 
 // Emission: per row, the winners in index order to the message at the row's offset, and e = +0
@@ -2904,9 +2950,10 @@ __global__ __launch_bounds__(kSelNT) void k_rowscan(Tables T, WSel ws0, Batch BT
 // of largest magnitude hold hundreds, 1 for one or a few workers and 4 for a batch.  A top-k row
 // with winning ties (flagged kAccRow) takes its elements in acc as its candidates.  The step's
 // last kernel, it also clears the overflow pool's counters for the next step.
-template <uint32_t RW, bool ACC_ROWS>
+template <int KIND, uint32_t RW, bool ONE>
 __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_idx, float* out_val, Batch BT,
-                                              int cand_zeroed) {
+                                              int cand_zeroed, uint32_t block_rows) {
+  constexpr bool ACC_ROWS = KIND == 0;
   static_assert(RW >= 1 && RW <= 64 && (RW & (RW - 1)) == 0, "one lane per row, a power of two");
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
   float* e_zero = BT.e[blockIdx.y];
@@ -2924,14 +2971,18 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
   // unless a candidate retry put acc back): losers get their values back, winners are left;
   // otherwise winners get +0.  A row emitted from acc whose candidates are +0 first puts them
   // back (rst, ocnt and oco: its own candidates).
-  uint32_t rl = 0, rst = 0, ocnt = 0, oco = 0;
+  uint32_t rl = 0, rst = 0, ocnt = 0, oco = 0, pbeg = 0, tb = 0;
+  bool last_row = false;  // of its segment
   if (has_row) {
-    const int l = T.L == 1 ? 0 : T.row_seg[myrow];  // one segment: no load before the record
+    const int l = ONE ? 0 : T.row_seg[myrow];  // one segment: no load before the record
     const uint32_t* R = res_of(ws, l);
     cnt = ws.counts[myrow];
     co = ws.coff[myrow];
     off = ws.roff[myrow];
+    pbeg = (uint32_t)T.seg_P[l];
     pend = (uint32_t)T.seg_P[l + 1];
+    tb = row_tile(T, myrow);
+    last_row = T.L == 1 ? myrow + 1u == (uint32_t)T.nrows : myrow + 1u == (uint32_t)T.seg_cbase[l + 1];
     Tk = R[R_T];
     IT = R[R_IT];
     const bool zrow = e_zero && (cand_zeroed || (ACC_ROWS && T.seg_zc[l] && !R[R_RETRY]));
@@ -2952,20 +3003,32 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
     if (R[R_SLOW]) {
       cnt = 0;
       rst = 0;
+      last_row = false;
     }
+  }
+  if (block_rows) {  // (a wavefront's rows lie in one block)
+    const uint32_t before = rows_before(ws, row0 / block_rows);
+    off += before;
   }
   const float* acc = BT.g[blockIdx.y] ? BT.e[blockIdx.y] : BT.src[blockIdx.y];
   if (ACC_ROWS && __ballot(rst != 0u)) {  // wave-uniform
     for (uint32_t u = 0; u < RW; ++u) {
       const uint32_t n = __shfl(rst, (int)u, 64) ? __shfl(ocnt, (int)u, 64) : 0u;
       const uint32_t b0 = __shfl(oco, (int)u, 64);
-      for (uint32_t j = lane; j < n; j += 64) e_zero[ws.cand_idx[(size_t)b0 + j]] = ws.cand_val[(size_t)b0 + j];
+      const uint32_t t0 = __shfl(tb, (int)u, 64);
+      for (uint32_t j = lane; j < n; j += 64) e_zero[t0 + ws.cand_loc[(size_t)b0 + j]] = ws.cand_val[(size_t)b0 + j];
     }
     __threadfence();  // before the rows' elements are read from acc
   }
   const uint32_t incl = wave_incl_scan(cnt);
-  const uint32_t total = __shfl(incl, 63, 64);
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
   const uint32_t pre = incl - cnt;  // this lane's row: first flattened candidate
+  const uint32_t copre = co - pre;
+  // what lane r holds of row r: the same for every row of one segment (lane 0 has a row)
+  auto of_row = [&](uint32_t x, uint32_t r) -> uint32_t {
+    return ONE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)x) : (uint32_t)__shfl(x, (int)r, 64);
+  };
+  auto tile_of = [&](uint32_t r) -> uint32_t { return ONE ? (row0 + r) * kTile : (uint32_t)__shfl(tb, (int)r, 64); };
   // The wave's loop; the form that tests for rows emitted from acc runs only in a wave holding one.
   auto run = [&](auto acc_rows) {
     constexpr bool AR = decltype(acc_rows)::value;
@@ -2978,19 +3041,20 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
         const uint32_t p = __shfl(pre, (int)(r + step), 64);
         if (f < total && p <= f) r += step;
       }
-      sl = __shfl(co, (int)r, 64) + (f - __shfl(pre, (int)r, 64));
+      sl = __shfl(copre, (int)r, 64) + f;
       ia = AR && __shfl(in_acc, (int)r, 64) != 0u;
     };
-    auto fetch = [&](uint32_t sl, bool ia, uint32_t& k, uint32_t& i, float& v) {
+    // the entry's key', its element within the row's tile (with kCertain where it wins anyhow) and value
+    auto fetch = [&](uint32_t sl, uint32_t t0, bool ia, uint32_t& k, uint32_t& i, float& v) {
       if (AR && ia) {
         v = acc[sl];
-        k = mag_key(v);
-        i = sl;
+        i = sl - t0;
       } else {
-        k = ws.cand_key[sl];
-        i = ws.cand_idx[sl];
         v = ws.cand_val[sl];
+        i = ws.cand_loc[sl];
       }
+      if constexpr (KIND == 0) k = mag_key(v);
+      else k = sl;  // the key is loaded for an undecided candidate only, when its pass comes
     };
     uint32_t done = 0;  // this lane's row: winners emitted in earlier passes
     uint32_t r, sl;
@@ -2998,28 +3062,37 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
     locate(lane, r, sl, ia);
     uint32_t k = 0, i = 0;
     float v = 0.0f;
-    if (lane < total) fetch(sl, ia, k, i, v);
+    {
+      const uint32_t t0 = tile_of(r);
+      if (lane < total) fetch(sl, t0, ia, k, i, v);
+    }
     for (uint32_t f0 = 0; f0 < total; f0 += 64) {
       const uint32_t f = f0 + lane;
       const bool in = f < total;
       const uint32_t rpre = __shfl(pre, (int)r, 64);
-      const uint32_t rTk = __shfl(Tk, (int)r, 64), rIT = __shfl(IT, (int)r, 64);
-      const uint32_t roffr = __shfl(off, (int)r, 64) + __shfl(done, (int)r, 64);
-      const uint32_t rpend = __shfl(pend, (int)r, 64), rrl = __shfl(rl, (int)r, 64);
-      const uint32_t ck = k, ci = i;
+      const uint32_t rTk = of_row(Tk, r), rIT = of_row(IT, r);
+      const uint32_t roffr = __shfl(off + done, (int)r, 64);
+      // (one segment: no row's candidates are +0 where another's are not, but a row emitted from acc)
+      const uint32_t rpend = of_row(pend, r), rrl = ONE && !AR ? of_row(rl, r) : (uint32_t)__shfl(rl, (int)r, 64);
+      const uint32_t rpbeg = of_row(pbeg, r);
+      const bool certain = KIND == 1 && (i & kCertain);
+      uint32_t ck = k;
+      if constexpr (KIND == 1) ck = in && !certain ? ws.cand_key[k] : 0u;
+      const uint32_t ci = tile_of(r) + (i & (kTile - 1u));
       const float cv = v;
       // the next pass's candidates, in flight while this pass is written
       uint32_t rn = 0, sn = 0;
       bool ian = false;
       locate(f + 64, rn, sn, ian);
-      if (f + 64 < total) fetch(sn, ian, k, i, v);
-      const bool win = in && (ck > rTk || (ck == rTk && ci < rIT));
+      const uint32_t tn = tile_of(rn);
+      if (f + 64 < total) fetch(sn, tn, ian, k, i, v);
+      const bool win = in && (certain || ck > rTk || (ck == rTk && ci < rIT));
       const uint64_t bw = __ballot(win);
       // this pass's lanes of row r before this lane: [lo_r, lane)
       const uint32_t lo_r = rpre > f0 ? rpre - f0 : 0u;
       const uint64_t below = (lane ? (~0ull >> (64 - lane)) : 0ull) & ~((lo_r ? (~0ull >> (64 - lo_r)) : 0ull));
       const uint32_t pos = roffr + (uint32_t)__popcll(bw & below);
-      if (win && pos < rpend) {
+      if (win && pos - rpbeg < rpend - rpbeg) {
         out_idx[pos] = ci;
         if (out_val) out_val[pos] = cv;
         if (e_zero && !rrl) e_zero[ci] = 0.0f;
@@ -3035,9 +3108,93 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
       }
       r = rn;
     }
+    if (block_rows && last_row && off + done != pend) atomicOr(ws.diag, kDiagCount);
   };
   if (ACC_ROWS && __ballot(in_acc != 0u)) run(std::true_type{});
   else run(std::false_type{});
+}
+
+// The same, one row per wavefront, for rows of many candidates: everything that the row's lanes share is
+// kept in scalar registers, the next chunk of 64 candidates in flight while one is written.
+template <int KIND>
+__global__ __launch_bounds__(kNT) void k_emit_row(Tables T, WSel ws0, uint32_t* out_idx, float* out_val, Batch BT,
+                                                  int cand_zeroed, uint32_t block_rows) {
+  const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
+  float* e_zero = BT.e[blockIdx.y];
+  out_idx = shifted(out_idx, (uint64_t)blockIdx.y * BT.msg * 4u);
+  out_val = out_val ? shifted(out_val, (uint64_t)blockIdx.y * BT.msg * 4u) : nullptr;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kNT / 64) + (threadIdx.x >> 6)));
+  if (row >= (uint32_t)T.nrows) return;
+  if (blockIdx.x == 0 && threadIdx.x < (unsigned)kPools) *pcnt_of(ws, threadIdx.x) = 0u;
+  const int l = T.L == 1 ? 0 : T.row_seg[row];
+  const uint32_t* R = res_of(ws, l);
+  // one segment: the first 64 candidates of the row's static slot, in the same round trip as its counts
+  // (used if the row's candidates are there)
+  const uint32_t cap0 = T.L == 1 ? min(ws.S, (uint32_t)T.d - row * kTile) : 0u;
+  float vn = lane < cap0 ? ws.cand_val[(size_t)row * ws.S + lane] : 0.0f;
+  uint32_t xn = lane < cap0 ? ws.cand_loc[(size_t)row * ws.S + lane] : 0u;
+  const uint32_t cw = ws.counts[row], Tk = R[R_T], IT = R[R_IT], tb = row_tile(T, row);
+  const uint32_t pbeg = (uint32_t)T.seg_P[l], pend = (uint32_t)T.seg_P[l + 1];
+  uint32_t off = ws.roff[row];
+  if (R[R_SLOW]) return;
+  if (block_rows) off += rows_before(ws, row / block_rows);
+  const bool zrow = e_zero && (cand_zeroed || (KIND == 0 && T.seg_zc[l] && !R[R_RETRY]));
+  const bool in_acc = KIND == 0 && (cw & kAccRow);
+  uint32_t cnt = cw & ~kAccRow, co = 0;
+  const float* acc = BT.g[blockIdx.y] ? BT.e[blockIdx.y] : BT.src[blockIdx.y];
+  if (in_acc) {
+    if (zrow) {  // its own candidates' values go back into acc first
+      const uint32_t oc = ws.rtie[row], oco = row_entry(T, ws, row, oc, ws.coff[row]);
+      if (oco != kDropped)
+        for (uint32_t j = lane; j < oc; j += 64) e_zero[tb + ws.cand_loc[(size_t)oco + j]] = ws.cand_val[(size_t)oco + j];
+      __threadfence();  // before the row's elements are read from acc
+    }
+    uint32_t hi;
+    row_bounds(T, row, co, hi);
+  } else {
+    co = row_entry(T, ws, row, cnt, ws.coff[row]);
+  }
+  const bool restore = zrow && !in_acc;  // losers get their values back; otherwise winners get +0
+  auto fetch = [&](uint32_t j0) {  // lane's candidate of the chunk
+    const uint32_t j = j0 + lane;
+    if (j < cnt) {
+      vn = in_acc ? acc[co + j] : ws.cand_val[(size_t)co + j];
+      xn = in_acc ? co + j - tb : ws.cand_loc[(size_t)co + j];
+    }
+  };
+  if (!(cap0 && !in_acc && co == row * ws.S)) fetch(0);
+  uint32_t done = 0;
+#pragma unroll 1
+  for (uint32_t j0 = 0; j0 < cnt; j0 += 64) {
+    const float v = vn;
+    const uint32_t x = xn, left = cnt - j0;
+    const uint64_t there = left >= 64u ? ~0ull : (1ull << left) - 1ull;
+    uint32_t k = mag_key(v);
+    if constexpr (KIND == 1) k = lane < left && !(x & kCertain) ? ws.cand_key[(size_t)co + j0 + lane] : 0u;
+    if (left > 64u) fetch(j0 + 64u);  // the next chunk, in flight while this one is written
+    const uint32_t i = tb + (x & (kTile - 1u));
+    uint64_t bw = __ballot(k > Tk);
+    const uint64_t eq = __ballot(k == Tk) & there;
+    if (eq) bw |= __ballot(k == Tk && i < IT);
+    if constexpr (KIND == 1) bw |= __ballot((x & kCertain) != 0u);
+    bw &= there;
+    const uint32_t at = off + done;  // the chunk's first winner
+    const uint32_t pos = at + lanes_below(bw);
+    done += (uint32_t)__popcll(bw);
+    // (a chunk's positions lie in the segment's part of the message unless its counts are wrong)
+    const bool safe = at >= pbeg && off + done <= pend;
+    if (safe && __builtin_amdgcn_inverse_ballot_w64(bw)) {
+      out_idx[pos] = i;
+      if (out_val) out_val[pos] = v;
+      if (e_zero && !restore) e_zero[i] = 0.0f;
+    }
+    if (restore && __builtin_amdgcn_inverse_ballot_w64(there & ~bw)) e_zero[i] = v;
+  }
+  if (block_rows && lane == 0) {
+    const bool last = T.L == 1 ? row + 1u == (uint32_t)T.nrows : row + 1u == (uint32_t)T.seg_cbase[l + 1];
+    if (last && off + done != pend) atomicOr(ws.diag, kDiagCount);
+  }
 }
 
 }  // namespace efs

@@ -47,8 +47,8 @@ struct Blob {
 };
 
 struct WsLayout {
-  size_t diag = 0, res = 0, hist = 0, samp = 0, counts = 0, rcnt = 0, roff = 0, rtie = 0, lcnt = 0, coff = 0, pcnt = 0,
-         cand_idx = 0, cand_val = 0, cand_key = 0, list_idx = 0, list_key = 0, total = 0;
+  size_t diag = 0, res = 0, hist = 0, samp = 0, counts = 0, rcnt = 0, roff = 0, rtie = 0, lcnt = 0, scnt = 0, coff = 0,
+         pcnt = 0, bsum = 0, cand_loc = 0, cand_val = 0, cand_key = 0, list_idx = 0, list_key = 0, total = 0;
   uint32_t S = 0, capB = 0;
 };
 
@@ -80,6 +80,7 @@ struct ef_layout {
   bool big = false;        // some k_l is large: row winners are counted by many workgroups
   bool rk_direct = false;  // random-k: every segment's rows and expected window fit k_select's LDS
   uint32_t rk_emit_rw = 16;  // random-k emission: rows per wavefront
+  double row_mean[2] = {0, 0};  // per op, candidates per row expected on average
   bool any_zc = false;       // some top-k segment stores +0 at its candidates in the fused pass
 
   Blob blob;
@@ -195,7 +196,7 @@ void ef_layout::build() {
     if (dl > kExactMax) all_exact = false;
   }
   K = P[n];
-  // many-workgroup row counting: a very large k_l, or a segment with more rows than k_select's
+  // row offsets over many workgroups: a very large k_l, or a segment with more rows than k_select's
   // workgroup scans quickly (one workgroup walking 244,141 rows took 0.5-0.9 ms at 1e9 elements)
   big = *std::max_element(k.begin(), k.end()) >= kBigK;
   for (int l = 0; l < n && !big; ++l)
@@ -222,7 +223,7 @@ void ef_layout::build() {
   {
     uint64_t bt = 0, br = 0, lsum = 0;
     std::vector<uint32_t> slot[2];  // per op, per segment: static slot entries per row
-    double musum = 0.0;             // random-k: expected candidates of the whole layout
+    double musum = 0.0, etsum = 0.0;  // random-k / top-k: expected candidates of the whole layout
     slot[0].assign(n, 64);
     slot[1].assign(n, 64);
     lbase.assign(n, 0);
@@ -262,6 +263,7 @@ void ef_layout::build() {
       slot[0][l] = round_slot(mt + 4.0 * std::sqrt(mt) + 32.0);
       slot[1][l] = round_slot(mr + 8.0 * std::sqrt(mr) + 32.0);
       musum += mu;
+      etsum += dl <= kExactMax ? kl : std::min(dl, et);
       bt += ct;
       br += cr;
       // lists: sub-list c takes the entries of the segment's rows c, c + 16, ...; each of the
@@ -290,7 +292,9 @@ void ef_layout::build() {
     // random-k emission: about 96 candidates per wavefront on average (16 rows of a few at low
     // density; at 1 % a wavefront of 16 rows walked ~650 candidates in turn)
     rk_emit_rw = 16;
-    while (rk_emit_rw > 1 && (double)rk_emit_rw * musum / (double)std::max(nrows, 1) > 96.0) rk_emit_rw /= 2;
+    row_mean[0] = etsum / (double)std::max(nrows, 1);
+    row_mean[1] = musum / (double)std::max(nrows, 1);
+    while (rk_emit_rw > 1 && (double)rk_emit_rw * row_mean[1] > 96.0) rk_emit_rw /= 2;
     pB[0] = (uint64_t)std::ceil((double)(bt + 49152 + kPools * 4096) * pool / kPools) * kPools;
     pB[1] = (uint64_t)std::ceil((double)(br + 49152 + kPools * 4096) * pool / kPools) * kPools;
     lists = lsum;
@@ -393,11 +397,13 @@ WsLayout ef_layout::ws_layout(int op) const {
   w.roff = take(rows * 4);
   w.rtie = take(rows * 4);
   w.lcnt = take((size_t)L * kSubLists * kLineWords * 4);
+  w.scnt = o == 1 && !rk_direct ? take((size_t)L * kSubLists * kLineWords * 4) : 0;
+  w.bsum = big ? take((size_t)kRowBlocks * 4) : 0;
   w.coff = take(rows * 4);
   w.pcnt = take((size_t)kPools * kLineWords * 4);
-  w.cand_idx = take(slots * 4);
+  w.cand_loc = take(slots * 2);
   w.cand_val = take(slots * 4);
-  w.cand_key = take(slots * 4);
+  w.cand_key = o == 1 ? take(slots * 4) : 0;
   w.list_idx = take(pairs ? slots * 8 : (size_t)lists * 4);
   w.list_key = take(pairs ? 0 : (size_t)lists * 4);
   w.total = at;
@@ -422,7 +428,9 @@ WSel make_ws(const WsLayout& l, void* base) {
   w.pcnt = reinterpret_cast<uint32_t*>(b + l.pcnt);
   w.pool0 = l.S;
   w.capB = l.capB;
-  w.cand_idx = reinterpret_cast<uint32_t*>(b + l.cand_idx);
+  w.scnt = reinterpret_cast<uint32_t*>(b + l.scnt);
+  w.bsum = reinterpret_cast<uint32_t*>(b + l.bsum);
+  w.cand_loc = reinterpret_cast<uint16_t*>(b + l.cand_loc);
   w.cand_val = reinterpret_cast<float*>(b + l.cand_val);
   w.cand_key = reinterpret_cast<uint32_t*>(b + l.cand_key);
   w.list_idx = reinterpret_cast<uint32_t*>(b + l.list_idx);
@@ -545,9 +553,9 @@ struct Steps {
 
 // Top-k (KIND 0): sample -> candidate rule -> fused accumulate + candidates -> bin of the k-th ->
 // collect -> exact threshold and row offsets -> emission.
-// Random-k (KIND 1): fused accumulate + Philox candidates -> collect (certain winners counted, the
-// window [ulo, tau) listed; on direct layouts by the streaming pass itself) -> exact threshold and
-// row offsets -> emission.
+// Random-k (KIND 1): fused accumulate + Philox candidates (certain winners counted) -> the window [ulo,
+// tau) listed (on direct layouts by the streaming pass itself) -> exact threshold and row offsets ->
+// emission.
 // Each phase runs for all W workers before the next: the streaming passes one launch per worker,
 // every other kernel once per kBatchMax workers (the worker is the grid's second dimension), so
 // the short latency-bound selection kernels are paid once for the batch.
@@ -607,16 +615,24 @@ int run_select(const ef_layout* L, const Steps& P, unsigned phases, void* stream
       const float* src = P.src[wk];
       const uint64_t seed = KIND == 1 && P.seeds ? P.seeds[wk] : 0u;
       const uint32_t s0 = (uint32_t)seed, s1 = (uint32_t)(seed >> 32), step = KIND == 1 ? P.step : 0u;
-      if (!P.g)
-        EF_LAUNCH((k_stream_sel<KIND, 0, false>), rgrid, rblk, 0, st, T, nullptr, src, nullptr, s0, s1, step, w);
-      else if (KIND == 0 && L->any_zc && P.g_dtype == EF_F32)
-        EF_LAUNCH((k_stream_sel<KIND, 0, true, true>), rgrid, rblk, 0, st, T, g_at(wk), src, e_at(wk), s0, s1, step, w);
-      else if (KIND == 0 && L->any_zc)
-        EF_LAUNCH((k_stream_sel<KIND, 1, true, true>), rgrid, rblk, 0, st, T, g_at(wk), src, e_at(wk), s0, s1, step, w);
-      else if (P.g_dtype == EF_F32)
-        EF_LAUNCH((k_stream_sel<KIND, 0, true>), rgrid, rblk, 0, st, T, g_at(wk), src, e_at(wk), s0, s1, step, w);
-      else
-        EF_LAUNCH((k_stream_sel<KIND, 1, true>), rgrid, rblk, 0, st, T, g_at(wk), src, e_at(wk), s0, s1, step, w);
+      const void* g = g_at(wk);
+      float* e = e_at(wk);
+      const bool f32 = P.g_dtype == EF_F32;
+      if constexpr (KIND == 0) {
+        if (!P.g) EF_LAUNCH((k_stream_sel<0, 0, false>), rgrid, rblk, 0, st, T, nullptr, src, nullptr, s0, s1, step, w);
+        else if (L->any_zc && f32) EF_LAUNCH((k_stream_sel<0, 0, true, true>), rgrid, rblk, 0, st, T, g, src, e, s0, s1, step, w);
+        else if (L->any_zc) EF_LAUNCH((k_stream_sel<0, 1, true, true>), rgrid, rblk, 0, st, T, g, src, e, s0, s1, step, w);
+        else if (f32) EF_LAUNCH((k_stream_sel<0, 0, true>), rgrid, rblk, 0, st, T, g, src, e, s0, s1, step, w);
+        else EF_LAUNCH((k_stream_sel<0, 1, true>), rgrid, rblk, 0, st, T, g, src, e, s0, s1, step, w);
+      } else if (L->rk_direct) {
+        if (!P.g) EF_LAUNCH((k_stream_sel<1, 0, false, false, true>), rgrid, rblk, 0, st, T, nullptr, src, nullptr, s0, s1, step, w);
+        else if (f32) EF_LAUNCH((k_stream_sel<1, 0, true, false, true>), rgrid, rblk, 0, st, T, g, src, e, s0, s1, step, w);
+        else EF_LAUNCH((k_stream_sel<1, 1, true, false, true>), rgrid, rblk, 0, st, T, g, src, e, s0, s1, step, w);
+      } else {
+        if (!P.g) EF_LAUNCH((k_stream_sel<1, 0, false>), rgrid, rblk, 0, st, T, nullptr, src, nullptr, s0, s1, step, w);
+        else if (f32) EF_LAUNCH((k_stream_sel<1, 0, true>), rgrid, rblk, 0, st, T, g, src, e, s0, s1, step, w);
+        else EF_LAUNCH((k_stream_sel<1, 1, true>), rgrid, rblk, 0, st, T, g, src, e, s0, s1, step, w);
+      }
       EF_TRY(launched());
     }
   }
@@ -626,50 +642,72 @@ int run_select(const ef_layout* L, const Steps& P, unsigned phases, void* stream
     const WSel w = ws_of(c0);
     const Batch bt = batch_of(c0, (int)nw);
     const dim3 sgrid((unsigned)L->L, nw);
-    // rows per wavefront of the collection and of the emission: top-k rows hold hundreds of
-    // candidates, so one row per wavefront for one or a few workers (the most parallel form) and,
-    // for a batch, two (collection) or four (emission) for fewer, fuller wavefronts (measured on
-    // 16 workers: collection 23.7 us with two, 25.8 with four; emission the same with two or
-    // four); random-k rows hold a few at low density, 16 per wavefront there, fewer as the density
-    // grows (rk_emit_rw)
-    // (one worker on a very large, sparse layout as well: 1e9 elements at 0.01-0.1 %, top-k
-    // emission 79-87 -> 28-39 us; at 1-10 %, with hundreds of candidates a row, it was slower)
+    // rows per wavefront of the collection: one for one or a few workers (the most parallel form), two
+    // for a batch (16 workers on ResNet-50: 23.7 us with two, 25.8 with four) and for one worker on a
+    // very large, sparse layout
     const bool wide = nw >= kWideBatch ||
                       ((uint64_t)nw * L->nrows >= kWideRows && (uint64_t)L->K <= 16ull * L->nrows);
-    const uint32_t emit_rw = KIND == 1 ? L->rk_emit_rw : wide ? 4u : 1u;
+    // emission, rows per wavefront.  Top-k: two for a batch (16 workers on ResNet-50: one 38.5 us, two
+    // 38, four 50, eight 82: its hot rows hold hundreds), four on a very large sparse layout (1e9
+    // elements at 0.01-0.1 %: 79-87 us with one, 28-39 with four).  Random-k: rk_emit_rw, and twice that
+    // as often as there are wavefronts enough and they hold no more than 400 candidates (1e9 elements
+    // at 1 %: 75 us with two rows, 61 with four, 57 with eight)
+    uint32_t emit_rw = nw >= kWideBatch ? 2u : wide ? 4u : 1u;
+    if (KIND == 1) {
+      emit_rw = L->rk_emit_rw;
+      while (emit_rw < 16u && (uint64_t)nw * L->nrows / emit_rw > 16384u && 2.0 * emit_rw * L->row_mean[1] <= 400.0)
+        emit_rw *= 2u;
+    }
     const uint32_t emit_rows = (kNT / 64) * emit_rw;
     const dim3 egrid((unsigned)((L->nrows + emit_rows - 1) / emit_rows), nw);
     uint32_t* idx = P.idx + (uint64_t)c0 * K;
     float* val = P.val ? P.val + (uint64_t)c0 * K : nullptr;  // none: a selection prepared ahead
-    if (KIND == 0 ? !L->all_exact : !L->rk_direct) {
-      if (KIND == 0) {
-        EF_LAUNCH(k_resolve, sgrid, sblk, 0, st, T, w, bt);
-        EF_TRY(launched());
-      }
+    if (KIND == 0 && !L->all_exact) {
+      EF_LAUNCH(k_resolve, sgrid, sblk, 0, st, T, w, bt);
+      EF_TRY(launched());
       const uint32_t crows = (kNT / 64) * (wide ? 2u : 1u);  // rows per workgroup
       const dim3 cgrid((unsigned)((L->nrows + crows - 1) / crows), nw);
-      if (wide) EF_LAUNCH((k_collect<KIND, 2>), cgrid, blk, 0, st, T, w, bt);
-      else EF_LAUNCH((k_collect<KIND, 1>), cgrid, blk, 0, st, T, w, bt);
+      if (wide) EF_LAUNCH(k_collect<2>, cgrid, blk, 0, st, T, w, bt);
+      else EF_LAUNCH(k_collect<1>, cgrid, blk, 0, st, T, w, bt);
       EF_TRY(launched());
     }
+    if (KIND == 1 && !L->rk_direct) {
+      const uint32_t crows = (kNT / 64) * kCollectRk;
+      EF_LAUNCH(k_collect_randk, dim3((unsigned)((L->nrows + crows - 1) / crows), nw), blk, 0, st, T, w, bt);
+      EF_TRY(launched());
+    }
+    uint32_t brows = 0;  // many rows: rows per block of k_rowsum
     if (L->big) {
       EF_LAUNCH((k_select<KIND, true>), sgrid, sblk, 0, st, T, w, idx, val, P.step, bt);
       EF_TRY(launched());
-      const dim3 cgrid1((unsigned)((L->nrows + kNT / 64 - 1) / (kNT / 64)), nw);  // a row per wavefront
-      EF_LAUNCH(k_rowcount<KIND>, cgrid1, blk, 0, st, T, w, bt);
-      EF_TRY(launched());
-      EF_LAUNCH(k_rowscan, sgrid, sblk, 0, st, T, w, bt);
+      if (KIND == 0) {
+        const dim3 cgrid1((unsigned)((L->nrows + kNT / 64 - 1) / (kNT / 64)), nw);  // a row per wavefront
+        EF_LAUNCH(k_rowcount, cgrid1, blk, 0, st, T, w, bt);
+        EF_TRY(launched());
+        EF_LAUNCH(k_rowtie, sgrid, sblk, 0, st, T, w, bt);
+        EF_TRY(launched());
+      }
+      const uint32_t per = kRowsumT * kRowBlocks;
+      brows = kRowsumT * (uint32_t)(((uint32_t)L->nrows + per - 1) / per);
+      EF_LAUNCH(k_rowsum<KIND>, dim3(((unsigned)L->nrows + brows - 1) / brows, nw), blk, 0, st, T, w, bt, brows);
     } else {
       EF_LAUNCH((k_select<KIND, false>), sgrid, sblk, 0, st, T, w, idx, val, P.step, bt);
     }
     EF_TRY(launched());
     const int cz = KIND == 1 && P.e ? 1 : 0;  // random-k, fused: the candidates were stored as +0
     // (top-k rows with winning ties are emitted from acc)
-    if (emit_rw == 16u) EF_LAUNCH((k_emit<16, KIND == 0>), egrid, blk, 0, st, T, w, idx, val, bt, cz);
-    else if (emit_rw == 8u) EF_LAUNCH((k_emit<8, KIND == 0>), egrid, blk, 0, st, T, w, idx, val, bt, cz);
-    else if (emit_rw == 4u) EF_LAUNCH((k_emit<4, KIND == 0>), egrid, blk, 0, st, T, w, idx, val, bt, cz);
-    else if (emit_rw == 2u) EF_LAUNCH((k_emit<2, KIND == 0>), egrid, blk, 0, st, T, w, idx, val, bt, cz);
-    else EF_LAUNCH((k_emit<1, KIND == 0>), egrid, blk, 0, st, T, w, idx, val, bt, cz);
+    const bool one = L->L == 1;
+#define EF_EMIT(RW)                                                                                          \
+  do {                                                                                                       \
+    if (one) EF_LAUNCH((k_emit<KIND, RW, true>), egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);          \
+    else EF_LAUNCH((k_emit<KIND, RW, false>), egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);             \
+  } while (0)
+    if (emit_rw == 16u) EF_EMIT(16);
+    else if (emit_rw == 8u) EF_EMIT(8);
+    else if (emit_rw == 4u) EF_EMIT(4);
+    else if (emit_rw == 2u) EF_EMIT(2);
+    else EF_LAUNCH(k_emit_row<KIND>, egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);
+#undef EF_EMIT
     EF_TRY(launched());
   }
   return EF_OK;
