@@ -1168,36 +1168,43 @@ __device__ __forceinline__ void for_keys(const K& keys, uint32_t n, F fn) {
   }
 }
 
-// A list in global memory, swept sub-list by sub-list: the position within a sub-list is the
-// address, where indexing the concatenation searched the sub-list bounds for every key (BERT flat
-// at 10 % with bf16 values: the selection kernel's sweeps of a 211,000-key list took 97 us that
-// way, the whole kernel 77 us this way).  fn(f, key) gets the position f in the concatenation.
+// A list in global memory, a wavefront per sub-list: the position within a sub-list is the address,
+// where indexing the concatenation searched the sub-list bounds for every key (BERT flat at 10 %
+// with bf16 values: the selection kernel's sweeps of a 211,000-key list took 97 us that way), and
+// no sub-list waits for another (swept one after another by the whole workgroup, 38,000 keys kept
+// two loads per thread in flight).  fn(f, key) gets the position f in the concatenation; fn2(f, key,
+// address) also where the key lies in the list arrays.
+static_assert(kSubLists == kSelNT / 64, "a wavefront per sub-list");
+template <int B = kBatch, typename F>
+__device__ __forceinline__ void for_keys2(const SubLists& L, F fn2) {
+  const uint32_t c = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  uint32_t m0 = 0, m1 = 0;  // the bounds of sub-list c, selected without indexing M
+#pragma unroll
+  for (int x = 0; x <= kSubLists; ++x) {
+    if (x == (int)c) m0 = L.M[x];
+    if (x == (int)c + 1) m1 = L.M[x];
+  }
+  const uint32_t nc = m1 - m0;
+  const size_t at = L.base + (size_t)c * L.q;
+  const uint32_t* a = L.arr + at;
+  for (uint32_t base = 0; base < nc; base += 64u * B) {
+    uint32_t k[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const uint32_t j = base + (uint32_t)u * 64u + lane;
+      k[u] = j < nc ? a[j] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const uint32_t j = base + (uint32_t)u * 64u + lane;
+      if (j < nc) fn2(m0 + j, k[u], at + j);
+    }
+  }
+}
 template <int B = kBatch, typename F>
 __device__ __forceinline__ void for_keys(const SubLists& L, uint32_t n, F fn) {
   (void)n;  // = L.M[kSubLists]
-  for (int c = 0; c < kSubLists; ++c) {
-    uint32_t m0 = 0, m1 = 0;  // the bounds of sub-list c, selected without indexing M
-#pragma unroll
-    for (int x = 0; x <= kSubLists; ++x) {
-      if (x == c) m0 = L.M[x];
-      if (x == c + 1) m1 = L.M[x];
-    }
-    const uint32_t nc = m1 - m0;
-    const uint32_t* a = L.arr + L.base + (size_t)c * L.q;
-    for (uint32_t base = 0; base < nc; base += (uint32_t)kSelNT * B) {
-      uint32_t k[B];
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const uint32_t j = base + (uint32_t)u * kSelNT + threadIdx.x;
-        k[u] = j < nc ? a[j] : 0u;
-      }
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const uint32_t j = base + (uint32_t)u * kSelNT + threadIdx.x;
-        if (j < nc) fn(m0 + j, k[u]);
-      }
-    }
-  }
+  for_keys2<B>(L, [&](uint32_t f, uint32_t k, size_t) { fn(f, k); });
 }
 
 // Exact selection over the whole segment (used when the candidates cannot contain the answer):
@@ -2057,7 +2064,11 @@ __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
   __shared__ uint32_t s_lk[kNT / 64][kCollectBuf], s_li[kNT / 64][kCollectBuf];
   const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint32_t row0 = (blockIdx.x * (kNT / 64) + (threadIdx.x >> 6)) * kCollectRows;
+  // a wavefront's rows lie far apart: crowded rows (a layer of large values) are neighbours, and one
+  // wavefront with several of them would hold the kernel up
+  const uint32_t stride = ((uint32_t)T.nrows + kCollectRows - 1u) / kCollectRows;
+  const uint32_t row0 = blockIdx.x * (kNT / 64) + (threadIdx.x >> 6);
+  if (row0 >= stride) return;
   int ls[kCollectRows];
   uint32_t cnts[kCollectRows], cofs[kCollectRows];
   float v0[kCollectRows];
@@ -2074,7 +2085,7 @@ __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
   }
 #pragma unroll
   for (uint32_t r = 0; r < kCollectRows; ++r) {
-    const uint32_t row = min(row0 + r, (uint32_t)T.nrows - 1u);
+    const uint32_t row = min(row0 + r * stride, (uint32_t)T.nrows - 1u);
     ls[r] = T.L == 1 ? 0 : T.row_seg[row];  // one segment: no load before the segment's record
     cnts[r] = ws.counts[row];
     cofs[r] = ws.coff[row];
@@ -2085,7 +2096,7 @@ __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
   }
 #pragma unroll
   for (uint32_t r = 0; r < kCollectRows; ++r) {
-    const uint32_t row = row0 + r;
+    const uint32_t row = row0 + r * stride;
     if (row >= (uint32_t)T.nrows) break;
     const int l = ls[r];
     uint32_t* R = res_of(ws, l);
@@ -2354,6 +2365,46 @@ __device__ __forceinline__ void list_threshold(const K& key, const K& idx, uint3
   list_threshold_ao(key, idx, m, need, kand, kor, hist, lds, g, T_out, IT_out, defer_need);
 }
 
+// Random-k, a list in global memory: its keys u = ~key' are uniform over [ulo, uhi], so the need-th
+// smallest of m lies within a few standard deviations of its expected rank.  The keys of that band go
+// to LDS (their number and that of the keys below it counted on the way), and the answer is found
+// among them.  False when the band missed it (six deviations: a chance below 10^-8) or does not fit;
+// the general search over the list follows.  1e9 elements at 1 %, 38,000 listed: the select kernel
+// 94 -> 57 us.  (Lists in LDS gain nothing from a band: ranking one directly in place of the radix
+// level took 11.8 us like before on flat 2^20 at 1 %.)
+__device__ __forceinline__ bool band_threshold(const SubLists& lk, const SubLists& li, uint32_t m, uint32_t need,
+                                               uint32_t ulo, uint32_t uhi, uint32_t* s_key, uint32_t* s_idx,
+                                               uint32_t cap, uint32_t* hist, uint32_t* lds, uint64_t* g,
+                                               uint32_t& T_out, uint32_t& IT_out) {
+  __shared__ uint32_t s_in, s_below;
+  const double span = (double)(uhi - ulo) + 1.0, per = span / (double)m;
+  const float x = (float)need / (float)m;
+  const double h = 6.0f * sqrtf(fmaxf((float)m * x * (1.0f - x), 0.0f)) + 8.0f;
+  const uint32_t b0 = ulo + (uint32_t)fmin(fmax(((double)need - h) * per, 0.0), span - 1.0);
+  const uint32_t b1 = ulo + (uint32_t)fmin(fmax(((double)need + h) * per, 0.0), span - 1.0);
+  if (threadIdx.x == 0) s_in = s_below = 0u;
+  __syncthreads();
+  uint32_t below = 0;
+  for_keys2(lk, [&](uint32_t, uint32_t k, size_t at) {
+    const uint32_t u = ~k;
+    below += u < b0 ? 1u : 0u;
+    if (u >= b0 && u <= b1) {
+      const uint32_t p = atomicAdd(&s_in, 1u);
+      if (p < cap) {
+        s_key[p] = k;
+        s_idx[p] = li.arr[at];
+      }
+    }
+  });
+  if (below) atomicAdd(&s_below, below);
+  __syncthreads();
+  const uint32_t n = s_in, before = s_below;
+  __syncthreads();
+  if (n > cap || need <= before || need > before + n) return false;  // uniform
+  list_threshold(s_key, s_idx, n, need - before, hist, lds, g, T_out, IT_out);
+  return true;
+}
+
 // Per segment: the exact threshold among the listed candidates, then every row's message offset;
 // or the exact whole-segment path when the candidates cannot hold the answer.  Independent loads
 // are issued together (record, sub-list sizes, the rows' counts) to keep the chain of dependent
@@ -2361,8 +2412,12 @@ __device__ __forceinline__ void list_threshold(const K& key, const K& idx, uint3
 // the list's winners added to their rows' counts with global atomics (the listed candidates are few
 // beside the winners, so that counting every row's winners again, 22 us on BERT flat at 10 % and 55 us
 // on 1e9 elements at 1 %, is not needed); k_rowsum turns the counts into offsets over many workgroups.
-template <int KIND, bool BIG>
-__global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t* out_idx, float* out_val,
+// SMALL: segments of at most kSmallRows rows, random-k on direct layouts only, lists expected to fit
+// kSmallList entries; two of its workgroups fit a CU (8 workers' random-k steps on ResNet-18's 62
+// layers, 496 workgroups: 24.7 -> 20.7 us).
+constexpr uint32_t kSmallList = 4096, kSmallRows = 4096;
+template <int KIND, bool BIG, bool SMALL = false>
+__global__ __launch_bounds__(kSelNT, SMALL ? 8 : 4) void k_select(Tables T, WSel ws0, uint32_t* out_idx, float* out_val,
                                                    uint32_t step, Batch BT) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
   float* e_zero = BT.e[blockIdx.y];
@@ -2370,12 +2425,13 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
   out_idx = shifted(out_idx, (uint64_t)blockIdx.y * BT.msg * 4u);
   out_val = out_val ? shifted(out_val, (uint64_t)blockIdx.y * BT.msg * 4u) : nullptr;
   const uint32_t s0 = BT.seed_lo[blockIdx.y], s1 = BT.seed_hi[blockIdx.y];
-  constexpr uint32_t kPer = kSelPer;  // rows per thread held in registers (more are re-read)
+  constexpr uint32_t kPer = SMALL ? kSmallRows / kSelNT : kSelPer;  // rows per thread held in registers (more are re-read)
   __shared__ uint32_t hist[kHBins];
   __shared__ uint32_t lds[3 * kSelNT / 64];
-  __shared__ uint32_t s_key[kListLds];
-  __shared__ uint32_t s_idx[kListLds];
-  __shared__ uint32_t s_add[BIG ? 1 : kRowsLds];
+  constexpr uint32_t kCap = SMALL ? kSmallList : kListLds, kRowCap = SMALL ? kSmallRows : kRowsLds;
+  __shared__ uint32_t s_key[kCap];
+  __shared__ uint32_t s_idx[kCap];
+  __shared__ uint32_t s_add[BIG ? 1 : kRowCap];
   __shared__ uint64_t s_g[kRankList];
   const int l = blockIdx.x;
   uint32_t* R = res_of(ws, l);
@@ -2396,7 +2452,7 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
     need = R[R_NEED];
     ovf = R[R_OVF];
   }
-  const bool direct = KIND == 1 && T.rk_direct;
+  const bool direct = KIND == 1 && (SMALL || T.rk_direct);
   const uint32_t lq = T.seg_lq[l];
   uint32_t lc[kSubLists];
 #pragma unroll
@@ -2483,7 +2539,7 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
     }
     // direct lists: the rows' undecided candidates (counts - certain) must fit the LDS list;
     // sub-lists: every one its region
-    slow = S > kl || N < kl || dropped != 0 || (direct ? N - S > kListLds : lfull);
+    slow = S > kl || N < kl || dropped != 0 || (direct ? N - S > kCap : lfull);
     need = kl - S;
     mU = N - S;
     if (threadIdx.x == 0) {
@@ -2511,7 +2567,7 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
     slow_select<KIND>(T, l, data, e_zero, out_idx, out_val, s0, s1, step, hist, lds);
     return;
   }
-  const bool rows_lds = nr <= kRowsLds;
+  const bool rows_lds = nr <= kRowCap;
   bool tie = false;
   bool done = KIND == 1;  // many rows: the rows' winner counts are complete
   if constexpr (KIND == 0) tie = listed && (R[R_B] == 0 || retry_ties);
@@ -2628,7 +2684,7 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
     }
     lk.M[kSubLists] = li.M[kSubLists] = m;
     if (direct) m = mU;
-    const bool in_lds = m <= kListLds;
+    const bool in_lds = (KIND == 1 && SMALL) || m <= kCap;  // (direct lists fit, else the segment is slow)
     // top-k, list staged in LDS: the AND and OR of its keys, taken as they pass through
     uint32_t sand = 0xFFFFFFFFu, sor = 0u;
     if (direct) {
@@ -2700,7 +2756,8 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
         // list finds (1.2 us on ResNet-50 flat) comes from the window itself
         const uint32_t klo = ~(uint32_t)(T.seg_tau[l] - 1u), khi = ~T.seg_ulo[l];
         if (in_lds) list_threshold_ao(s_key, s_idx, m, need, klo, khi, hist, lds, s_g, Tk, IT, defer);
-        else list_threshold_ao(lk, li, m, need, klo, khi, hist, lds, s_g, Tk, IT, defer);
+        else if (!band_threshold(lk, li, m, need, ~khi, ~klo, s_key, s_idx, kCap, hist, lds, s_g, Tk, IT))
+          list_threshold_ao(lk, li, m, need, klo, khi, hist, lds, s_g, Tk, IT, defer);
       } else if (in_lds) {
         // (the AND / OR taken while staging the list spares a sweep over it: 1.1 us on ResNet-50)
         if (m > kRankList) block_and_or(sand, sor, lds);
@@ -2712,12 +2769,23 @@ __global__ __launch_bounds__(kSelNT) void k_select(Tables T, WSel ws0, uint32_t*
       // rows are counted again by k_rowcount)
       const uint32_t c0 = o / kTile;
       if constexpr (BIG) done = IT != kTieRows && (KIND == 1 || in_lds);
-      for (uint32_t j = threadIdx.x; j < (!BIG || done ? m : 0u); j += kSelNT) {
-        const uint32_t k = in_lds ? s_key[j] : lk[j];
-        const uint32_t i = in_lds ? s_idx[j] : li[j];
-        if (k > Tk || (k == Tk && i < IT)) {
-          if (!BIG && rows_lds) atomicAdd(&s_add[i / kTile - c0], 1u);
-          else atomicAdd(&ws.rcnt[r0 + (i / kTile - c0)], 1u);
+      auto join = [&](uint32_t i) {
+        if (!BIG && rows_lds) atomicAdd(&s_add[i / kTile - c0], 1u);
+        else atomicAdd(&ws.rcnt[r0 + (i / kTile - c0)], 1u);
+      };
+      if (!BIG || done) {
+        if (in_lds) {
+          for (uint32_t j = threadIdx.x; j < m; j += kSelNT) {
+            const uint32_t k = s_key[j], i = s_idx[j];
+            if (k > Tk || (k == Tk && i < IT)) join(i);
+          }
+        } else {
+          for_keys2(lk, [&](uint32_t, uint32_t k, size_t at) {
+            if (k >= Tk) {
+              const uint32_t i = li.arr[at];
+              if (k > Tk || i < IT) join(i);
+            }
+          });
         }
       }
     }

@@ -81,6 +81,7 @@ struct ef_layout {
   bool rk_direct = false;  // random-k: every segment's rows and expected window fit k_select's LDS
   uint32_t rk_emit_rw = 16;  // random-k emission: rows per wavefront
   double row_mean[2] = {0, 0};  // per op, candidates per row expected on average
+  bool sel_small[2] = {false, false};  // per op: the select kernel's SMALL form
   bool any_zc = false;       // some top-k segment stores +0 at its candidates in the fused pass
 
   Blob blob;
@@ -210,6 +211,16 @@ void ef_layout::build() {
     const double wm = (double)(tau[l] - ulo[l]) / 4294967296.0 * dl;
     if (cbase[l + 1] - cbase[l] > (int32_t)(kSelNT * kSelPer) || wm + 8.0 * std::sqrt(wm) + 16.0 > (double)kListLds)
       rk_direct = false;
+  }
+  // the select kernel's form of less LDS: few rows per segment, and random-k's lists (always in LDS on
+  // direct layouts) small enough; a top-k list that does not fit is read from global memory
+  sel_small[0] = true;
+  sel_small[1] = rk_direct;
+  for (int l = 0; l < n; ++l) {
+    const double dl = (double)(off64[l + 1] - off64[l]);
+    const double wm = (double)(tau[l] - ulo[l]) / 4294967296.0 * dl;
+    if (cbase[l + 1] - cbase[l] > (int32_t)kSmallRows) sel_small[0] = sel_small[1] = false;
+    if (wm + 8.0 * std::sqrt(wm) + 16.0 > (double)kSmallList) sel_small[1] = false;
   }
   nrows = cbase[n];
   nruns = ro[n];
@@ -665,8 +676,9 @@ int run_select(const ef_layout* L, const Steps& P, unsigned phases, void* stream
     if (KIND == 0 && !L->all_exact) {
       EF_LAUNCH(k_resolve, sgrid, sblk, 0, st, T, w, bt);
       EF_TRY(launched());
-      const uint32_t crows = (kNT / 64) * (wide ? 2u : 1u);  // rows per workgroup
-      const dim3 cgrid((unsigned)((L->nrows + crows - 1) / crows), nw);
+      // (k_collect's wavefronts: one per row, or per two rows half the rows apart)
+      const uint32_t cw = ((uint32_t)L->nrows + (wide ? 1u : 0u)) / (wide ? 2u : 1u);
+      const dim3 cgrid((cw + kNT / 64 - 1) / (kNT / 64), nw);
       if (wide) EF_LAUNCH(k_collect<2>, cgrid, blk, 0, st, T, w, bt);
       else EF_LAUNCH(k_collect<1>, cgrid, blk, 0, st, T, w, bt);
       EF_TRY(launched());
@@ -690,6 +702,8 @@ int run_select(const ef_layout* L, const Steps& P, unsigned phases, void* stream
       const uint32_t per = kRowsumT * kRowBlocks;
       brows = kRowsumT * (uint32_t)(((uint32_t)L->nrows + per - 1) / per);
       EF_LAUNCH(k_rowsum<KIND>, dim3(((unsigned)L->nrows + brows - 1) / brows, nw), blk, 0, st, T, w, bt, brows);
+    } else if (L->sel_small[KIND]) {
+      EF_LAUNCH((k_select<KIND, false, true>), sgrid, sblk, 0, st, T, w, idx, val, P.step, bt);
     } else {
       EF_LAUNCH((k_select<KIND, false>), sgrid, sblk, 0, st, T, w, idx, val, P.step, bt);
     }

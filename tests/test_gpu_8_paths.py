@@ -4,8 +4,9 @@ Bit-exact against the CPU oracle, through the C ABI."""
 import numpy as np
 import pytest
 
-from efs_gpu import Case, announce, assert_f32_equal, dev
+from efs_gpu import Case, announce, assert_f32_equal, certify_randk, certify_topk, dev, host
 from oracle import efsparse_oracle as O
+from workloads.generate import to_bf16_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +45,46 @@ def test_sparse_aggregate_tile_entries(counts):
         E.decompress_aggregate(c.L, E.EF_MSG_SPARSE, W, dev(idx.view(np.int32)), dev(val), out,
                                c.L.workspace(E.EF_OP_AGG_SPARSE, W), average)
         assert_f32_equal(out, O.decompress_aggregate_sparse(d, idx, val, average), f"average={average}")
+
+
+# random-k on one segment: the last row count and the last window of the select kernel's small form and
+# of direct lists, the first of each larger form, and a list in global memory with the rows' offsets from
+# one block of rows and from several
+@pytest.mark.parametrize("d,density", [(4096 * 4096, 0.001), (4096 * 4096 + 1, 0.001), (1 << 20, 0.1), (1 << 20, 0.12),
+                                       (1 << 22, 0.1), (1 << 23, 0.1), (4096 * 16384, 0.01), (4096 * 16384 + 5, 0.01)])
+def test_randk_select_forms(d, density):
+    import paper_2009_09271_amd as E
+    import torch
+    announce("random-k forms", d, density)
+    c = Case([0, d], density)
+    rng = np.random.default_rng(d % 1000)
+    acc = rng.standard_normal(d, dtype=np.float32) + np.float32(0.0)  # (no -0: it leaves g + e as +0)
+    e = torch.zeros(d, dtype=torch.float32, device="cuda")
+    idx, val, ws = c.step("randk", acc, e, seed=77 + d, step=3)
+    assert c.L.diag(ws, E.EF_OP_RANDK) == 0
+    certify_randk(acc, c.offs, c.ks, host(idx), host(val), host(e), 77 + d, 3)
+
+
+# top-k candidates of 1 to 4096 a row, spread over rows of every kind (a wavefront's chunks of 64, the
+# static slot and the overflow pool, histogram in LDS or not, the last bin), with equal magnitudes
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,density", [(4096 * 70 + 13, 0.0005), (4096 * 70 + 13, 0.012), (4096 * 70, 0.1), (4096 * 520 + 1, 0.5),
+                                       (4096 * 16390, 0.03)])
+def test_topk_crowded_rows(d, density, dtype):
+    import paper_2009_09271_amd as E
+    import torch
+    announce("top-k crowded rows", d, density, dtype)
+    c = Case([0, d], density)
+    rng = np.random.default_rng(d % 997)
+    g = rng.standard_normal(d, dtype=np.float32)
+    for r in range(0, d // 4096, 7):  # every seventh row louder, by up to a factor of 64
+        g[r * 4096:(r + 1) * 4096] *= np.float32(2.0 ** (r % 7))
+    g[rng.random(d) < 0.2] = 0.25
+    g += np.float32(0.0)  # (no -0: it leaves g + e as +0)
+    if dtype == "bf16":
+        g16 = to_bf16_bits(g)
+        g = (g16.astype(np.uint32) << 16).view(np.float32)
+    e = torch.zeros(d, dtype=torch.float32, device="cuda")
+    idx, val, ws = c.step("topk", g16 if dtype == "bf16" else g, e)
+    assert c.L.diag(ws, E.EF_OP_TOPK) & 4 == 0
+    certify_topk(g, c.offs, c.ks, host(idx), host(val), host(e))
