@@ -1402,9 +1402,7 @@ __device__ __forceinline__ void hist_add_peel(uint32_t* h, uint32_t b) {
 // sample's would (runs of contiguous elements, by contrast, sample a handful of clusters: a small
 // tensor is either missed or over-represented many times).  Sample q = run * kSampleRun + thread;
 // the runs of a sampled segment also clear its candidate histogram (kHCopies * kHBins words).
-static_assert(kHCopies * kHBins == kSampleMax, "a sampled segment's histogram is cleared by its samples");
-static_assert(kExactMax <= kSampleMax, "a segment sampled whole fits the sample keys held in LDS");
-constexpr int kSampleKeysPer = kSampleMax / kSelNT;  // sample keys per thread, loaded in one round trip
+static_assert(kExactMax % kSelNT == 0, "whole sample keys per thread");
 static_assert(2 * kRankList <= kHBins, "the ranked entries (64-bit words) of an exact segment fit a histogram array");
 
 // Positions 0, 1, ... as the indices of keys held in position order.
@@ -1465,7 +1463,7 @@ __global__ __launch_bounds__(kSampleRun) void k_sample_gather(Tables T, WSel ws0
 //    bins there are as narrow as the sample allows (mode 0).
 __global__ __launch_bounds__(kSelNT) void k_sample_select(Tables T, WSel ws0, Batch BT) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
-  __shared__ uint32_t keys[kSampleMax];
+  __shared__ uint32_t keys[kExactMax];
   __shared__ uint32_t hist[kHBins];
   __shared__ __align__(8) uint32_t hist2[kHBins];
   __shared__ uint32_t lds[2 * kSelNT / 64];
@@ -1475,7 +1473,7 @@ __global__ __launch_bounds__(kSelNT) void k_sample_select(Tables T, WSel ws0, Ba
   uint32_t* R = res_of(ws, l);
   if (n <= (uint32_t)kExactMax) {
     uint32_t kand = 0xFFFFFFFFu, kor = 0u;
-    for_keys<kSampleKeysPer>(sk, n, [&](uint32_t f, uint32_t k) {
+    for_keys<kExactMax / kSelNT>(sk, n, [&](uint32_t f, uint32_t k) {
       keys[f] = k;
       kand &= k;
       kor |= k;
@@ -1497,61 +1495,88 @@ __global__ __launch_bounds__(kSelNT) void k_sample_select(Tables T, WSel ws0, Ba
     }
     return;
   }
-  // sampled: bins of the top 11 key bits (8 exponent + 3 mantissa bits); keys stay in registers
+  // sampled: bins of the top 11 key bits (8 exponent + 3 mantissa bits)
   const uint32_t ns = ((uint32_t)T.seg_ro[l + 1] - (uint32_t)T.seg_ro[l]) * kSampleRun;  // samples
   for (int b = threadIdx.x; b < kHBins; b += kSelNT) hist[b] = 0;
   __syncthreads();
-  uint32_t kmax = 0u;
-  // (the enlarged samples of dense layouts: the peeled add; a 16,384-key sample of ResNet-50's
-  // gradients took 1 us longer with it than with an atomic per key)
-  const bool peel = ns > (uint32_t)kSampleTotal;
-  for_keys<kSampleKeysPer>(sk, ns, [&](uint32_t, uint32_t k) {
-    if (peel) hist_add_peel(hist, k >> 20);
-    else atomicAdd(&hist[k >> 20], 1u);
-    kmax = max(kmax, k);
-  });
-  __syncthreads();
-  kmax = block_max_u32(kmax, lds);
-  // Key edge of the rank-th largest sampled key: the lower (or upper) edge of its top-11-bit bin,
-  // refined by the next 11 bits when that bin holds more than 64 sampled keys (concentrated
-  // values: an unrefined edge could take up to the whole bin's keys as candidates beyond the
-  // rank, which the candidate pool is not sized for).  Both ranks' bins come from one scan of
-  // the histogram.
-  const uint32_t rank = (uint32_t)T.seg_srank[l], urank = (uint32_t)T.seg_urank[l];
-  int bin_t, bin_u;
-  uint32_t above_t, above_u;
-  block_resolve2<kSelNT>(hist, kHBins, rank < ns ? rank : 0u, urank, lds, bin_t, above_t, bin_u, above_u);
-  auto rank_edge = [&](int bin, uint32_t above, uint32_t rk, bool upper) -> uint32_t {
-    if (bin < 0) return 0u;
-    if (hist[bin] <= 64u) return ((uint32_t)bin + (upper ? 1u : 0u)) << 20;
-    for (int b = threadIdx.x; b < kHBins; b += kSelNT) hist2[b] = 0;
-    __syncthreads();
-    for_keys(sk, ns, [&](uint32_t, uint32_t k) {
-      if ((k >> 20) == (uint32_t)bin) atomicAdd(&hist2[(k >> 9) & (kHBins - 1)], 1u);
+  // Samples of up to NK keys per thread stay in registers through the refinements (a 65,536-key sample
+  // read again for each edge: BERT flat at 10 %, 27.1 us for this kernel, 22.7 now); larger ones are read
+  // again.
+  auto rule = [&](auto per) {
+    constexpr int NK = decltype(per)::value;
+    uint32_t k[NK > 0 ? NK : 1];
+    if constexpr (NK > 0) {
+#pragma unroll
+      for (int u = 0; u < NK; ++u) {
+        const uint32_t f = (uint32_t)u * kSelNT + threadIdx.x;
+        k[u] = f < ns ? sk[f] : 0u;
+      }
+    }
+    // every sampled key in turn, f < ns
+    auto each = [&](auto fn) {
+      if constexpr (NK > 0) {
+#pragma unroll
+        for (int u = 0; u < NK; ++u)
+          if ((uint32_t)u * kSelNT + threadIdx.x < ns) fn(k[u]);
+      } else {
+        for_keys(sk, ns, [&](uint32_t, uint32_t x) { fn(x); });
+      }
+    };
+    uint32_t kmax = 0u;
+    // (the enlarged samples of dense layouts: the peeled add; a 16,384-key sample of ResNet-50's
+    // gradients took 1 us longer with it than with an atomic per key)
+    each([&](uint32_t x) {
+      if constexpr (NK == 0 || NK > kSampleTotal / kSelNT) hist_add_peel(hist, x >> 20);
+      else atomicAdd(&hist[x >> 20], 1u);
+      kmax = max(kmax, x);
     });
     __syncthreads();
-    uint32_t above2;
-    const int bin2 = block_resolve<kSelNT>(hist2, kHBins, rk - above, lds, above2);
-    return ((uint32_t)bin << 20) + (((uint32_t)max(bin2, 0) + (upper ? 1u : 0u)) << 9);
+    kmax = block_max_u32(kmax, lds);
+    // Key edge of the rank-th largest sampled key: the lower (or upper) edge of its top-11-bit bin,
+    // refined by the next 11 bits when that bin holds more than 64 sampled keys (concentrated
+    // values: an unrefined edge could take up to the whole bin's keys as candidates beyond the
+    // rank, which the candidate pool is not sized for).  Both ranks' bins come from one scan of
+    // the histogram.
+    const uint32_t rank = (uint32_t)T.seg_srank[l], urank = (uint32_t)T.seg_urank[l];
+    int bin_t, bin_u;
+    uint32_t above_t, above_u;
+    block_resolve2<kSelNT>(hist, kHBins, rank < ns ? rank : 0u, urank, lds, bin_t, above_t, bin_u, above_u);
+    auto rank_edge = [&](int bin, uint32_t above, uint32_t rk, bool upper) -> uint32_t {
+      if (bin < 0) return 0u;
+      if (hist[bin] <= 64u) return ((uint32_t)bin + (upper ? 1u : 0u)) << 20;
+      for (int b = threadIdx.x; b < kHBins; b += kSelNT) hist2[b] = 0;
+      __syncthreads();
+      each([&](uint32_t x) {
+        if ((x >> 20) == (uint32_t)bin) atomicAdd(&hist2[(x >> 9) & (kHBins - 1)], 1u);
+      });
+      __syncthreads();
+      uint32_t above2;
+      const int bin2 = block_resolve<kSelNT>(hist2, kHBins, rk - above, lds, above2);
+      return ((uint32_t)bin << 20) + (((uint32_t)max(bin2, 0) + (upper ? 1u : 0u)) << 9);
+    };
+    // rank >= sample size: every element is a candidate
+    const uint32_t thr = rank < ns ? rank_edge(bin_t, above_t, rank, false) : 0u;
+    // the bins resolve the range up to the upper edge of where the k-th key very likely lies
+    uint32_t top = rank_edge(bin_u, above_u, urank, true);
+    if (top <= thr || top > kmax) top = kmax;
+    const uint32_t span = top - thr;
+    // the least shift whose bins 1 .. kHBins - 2 hold the span (2^11 - 2 of them: span < 2^b gives at
+    // most 2^10 bins with a shift of b - 10, and one bit less where that still fits)
+    uint32_t sh = span < 1024u ? 0u : (uint32_t)(32 - __clz(span)) - 10u;
+    if (sh && (span >> (sh - 1u)) < (uint32_t)kHBins - 2u) --sh;
+    if (threadIdx.x == 0) {
+      R[R_A] = thr;
+      R[R_IA] = 0xFFFFFFFFu;
+      R[R_SH] = sh;
+      R[R_MODE] = 0;
+      R[R_SLOW] = 0;
+      R[R_OVF] = 0;
+    }
   };
-  // rank >= sample size: every element is a candidate
-  const uint32_t thr = rank < ns ? rank_edge(bin_t, above_t, rank, false) : 0u;
-  // the bins resolve the range up to the upper edge of where the k-th key very likely lies
-  uint32_t top = rank_edge(bin_u, above_u, urank, true);
-  if (top <= thr || top > kmax) top = kmax;
-  const uint32_t span = top - thr;
-  // the least shift whose bins 1 .. kHBins - 2 hold the span (2^11 - 2 of them: span < 2^b gives at
-  // most 2^10 bins with a shift of b - 10, and one bit less where that still fits)
-  uint32_t sh = span < 1024u ? 0u : (uint32_t)(32 - __clz(span)) - 10u;
-  if (sh && (span >> (sh - 1u)) < (uint32_t)kHBins - 2u) --sh;
-  if (threadIdx.x == 0) {
-    R[R_A] = thr;
-    R[R_IA] = 0xFFFFFFFFu;
-    R[R_SH] = sh;
-    R[R_MODE] = 0;
-    R[R_SLOW] = 0;
-    R[R_OVF] = 0;
-  }
+  if (ns <= 4u * kSelNT) rule(std::integral_constant<int, 4>{});
+  else if (ns <= (uint32_t)kSampleTotal) rule(std::integral_constant<int, kSampleTotal / kSelNT>{});
+  else if (ns <= (uint32_t)kSampleCap) rule(std::integral_constant<int, kSampleCap / kSelNT>{});
+  else rule(std::integral_constant<int, 0>{});
 }
 
 // ---------------------------------------------------------------------------------------------

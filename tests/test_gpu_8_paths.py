@@ -88,3 +88,4 @@ def test_topk_crowded_rows(d, density, dtype):
     idx, val, ws = c.step("topk", g16 if dtype == "bf16" else g, e)
     assert c.L.diag(ws, E.EF_OP_TOPK) & 4 == 0
     certify_topk(g, c.offs, c.ks, host(idx), host(val), host(e))
+
