@@ -2188,18 +2188,26 @@ __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
 }
 
 // Random-k without direct lists, per row: the undecided candidates ([ulo, tau)) go to the segment's
-// sub-lists, the certain winners are added to the segment's counters.  A wavefront looks at
-// kCollectRk rows' counts and reads the candidates of those that hold an undecided one only (1e9
-// elements at 1 %: one row in seven; every candidate's key read and tested took 65 us).
-constexpr uint32_t kCollectRk = 64;  // a lane each
+// sub-lists, the certain winners are added to the segment's counters.  A wavefront looks at rw rows'
+// counts (a lane each) and reads the candidates of those that hold an undecided one only (1e9 elements
+// at 1 %: one row in seven; every candidate's key read and tested took 65 us).  Those rows are read one
+// after another, four loads in flight, so rw is as large as leaves kCollectWaves wavefronts: at 64 rows
+// each, 2100 rows of 380 candidates made 33 wavefronts and the step took 257 us, now 64 (8.6e6 elements at
+// 9.4 %; 36.6e6 at 0.33 %: 119 us, now 98; 1e9 at 1 % keeps 64 rows).
+constexpr uint32_t kCollectWaves = 2048;
+inline uint32_t collect_rows(uint64_t rows) {
+  uint32_t rw = 64;
+  while (rw > 1u && rows / rw < kCollectWaves) rw /= 2u;
+  return rw;
+}
 constexpr uint32_t kCollectWide = 1024;  // segments of at least this many rows: a wavefront reserves list space once
-__global__ __launch_bounds__(kNT) void k_collect_randk(Tables T, WSel ws0, Batch BT) {
+__global__ __launch_bounds__(kNT) void k_collect_randk(Tables T, WSel ws0, Batch BT, uint32_t rw) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t row0 = (blockIdx.x * (kNT / 64) + (threadIdx.x >> 6)) * kCollectRk;
+  const uint32_t wave = blockIdx.x * (kNT / 64) + (threadIdx.x >> 6), row0 = wave * rw;
   if (row0 >= (uint32_t)T.nrows) return;
   const uint32_t row = min(row0 + lane, (uint32_t)T.nrows - 1u);
-  const bool has = lane < kCollectRk && row0 + lane < (uint32_t)T.nrows;
+  const bool has = lane < rw && row0 + lane < (uint32_t)T.nrows;
   int l = 0;
   uint32_t cnt = 0, cert = 0, co = kDropped, tb = 0, sub = 0;
   if (has) {
@@ -2214,7 +2222,7 @@ __global__ __launch_bounds__(kNT) void k_collect_randk(Tables T, WSel ws0, Batch
   const int l0 = __builtin_amdgcn_readfirstlane(l);  // (the first row: lane 0 has one)
   if (__ballot(has && l != l0) == 0) {  // rows of one segment: one addition
     const uint32_t s = wave_incl_scan(cert);
-    if (lane == 63 && s) atomicAdd(scnt_of(ws, l0, (row0 / kCollectRk) % kSubLists), s);
+    if (lane == 63 && s) atomicAdd(scnt_of(ws, l0, wave % kSubLists), s);
   } else if (has && cert) {
     atomicAdd(scnt_of(ws, l, sub), cert);
   }
@@ -2224,7 +2232,7 @@ __global__ __launch_bounds__(kNT) void k_collect_randk(Tables T, WSel ws0, Batch
   if (__ballot(has && l != l0) == 0 && (uint32_t)(T.seg_cbase[l0 + 1] - T.seg_cbase[l0]) >= kCollectWide) {
     const uint32_t und = list ? cnt - cert : 0u, inc = wave_incl_scan(und);
     const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-    sub = (row0 / kCollectRk) % kSubLists;
+    sub = wave % kSubLists;
     if (all && lane == 0) at = atomicAdd(lcnt_of(ws, l0, sub), all);
     at = (uint32_t)__builtin_amdgcn_readlane((int)at, 0) + inc - und;
   } else if (list) {
@@ -2239,16 +2247,28 @@ __global__ __launch_bounds__(kNT) void k_collect_randk(Tables T, WSel ws0, Batch
     const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)tb, j), lq = T.seg_lq[rl];
     const size_t sb = sublist_base(T, rl, (uint32_t)__builtin_amdgcn_readlane((int)sub, j));
     uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)at, j);
-    for (uint32_t f0 = 0; f0 < n; f0 += 64) {
-      const uint32_t f = f0 + lane;
-      const uint32_t x = f < n ? ws.cand_loc[(size_t)c0 + f] : kCertain;
-      const uint64_t b = __ballot(!(x & kCertain));
-      const uint32_t t = p + lanes_below(b);
-      if (!(x & kCertain) && t < lq) {  // a full sub-list is seen by k_select (its count exceeds lq)
-        ws.list_key[sb + t] = ws.cand_key[(size_t)c0 + f];
-        ws.list_idx[sb + t] = t0 + x;
+    for (uint32_t f0 = 0; f0 < n; f0 += 256) {
+      uint32_t x[4], k[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t f = f0 + (uint32_t)u * 64u + lane;
+        x[u] = f < n ? ws.cand_loc[(size_t)c0 + f] : kCertain;
       }
-      p += (uint32_t)__popcll(b);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t f = f0 + (uint32_t)u * 64u + lane;
+        k[u] = !(x[u] & kCertain) ? ws.cand_key[(size_t)c0 + f] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint64_t b = __ballot(!(x[u] & kCertain));
+        const uint32_t t = p + lanes_below(b);
+        if (!(x[u] & kCertain) && t < lq) {  // a full sub-list is seen by k_select (its count exceeds lq)
+          ws.list_key[sb + t] = k[u];
+          ws.list_idx[sb + t] = t0 + x[u];
+        }
+        p += (uint32_t)__popcll(b);
+      }
     }
   }
 }

@@ -684,8 +684,8 @@ int run_select(const ef_layout* L, const Steps& P, unsigned phases, void* stream
       EF_TRY(launched());
     }
     if (KIND == 1 && !L->rk_direct) {
-      const uint32_t crows = (kNT / 64) * kCollectRk;
-      EF_LAUNCH(k_collect_randk, dim3((unsigned)((L->nrows + crows - 1) / crows), nw), blk, 0, st, T, w, bt);
+      const uint32_t rw = collect_rows((uint64_t)nw * L->nrows), crows = (kNT / 64) * rw;
+      EF_LAUNCH(k_collect_randk, dim3((unsigned)((L->nrows + crows - 1) / crows), nw), blk, 0, st, T, w, bt, rw);
       EF_TRY(launched());
     }
     uint32_t brows = 0;  // many rows: rows per block of k_rowsum

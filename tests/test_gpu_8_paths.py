@@ -49,9 +49,10 @@ def test_sparse_aggregate_tile_entries(counts):
 
 # random-k on one segment: the last row count and the last window of the select kernel's small form and
 # of direct lists, the first of each larger form, and a list in global memory with the rows' offsets from
-# one block of rows and from several
+# one block of rows and from several; one row, several and the most to a collecting wavefront
 @pytest.mark.parametrize("d,density", [(4096 * 4096, 0.001), (4096 * 4096 + 1, 0.001), (1 << 20, 0.1), (1 << 20, 0.12),
-                                       (1 << 22, 0.1), (1 << 23, 0.1), (4096 * 16384, 0.01), (4096 * 16384 + 5, 0.01)])
+                                       (1 << 22, 0.1), (1 << 23, 0.1),
+                                       (4096 * 1100 + 7, 0.1), (4096 * 2740 + 9, 0.09), (4096 * 9000 + 1, 0.003), (4096 * 16384, 0.01), (4096 * 16384 + 5, 0.01)])
 def test_randk_select_forms(d, density):
     import paper_2009_09271_amd as E
     import torch
