@@ -50,6 +50,7 @@ enum : int {
   R_OVF = 11,   // candidates did not fit the workspace (top-k: a retry collects them again, else the
                 //   exact path runs)
   R_DONE = 12,  // top-k, many rows: the rows' winner counts are complete (k_rowcount has nothing to do)
+  R_Z = 13,     // top-k segments with seg_zc: the fused pass stored +0 at the candidates of keys from it on
 };
 
 constexpr int kBtWords = 8;  // words per record of the block aggregate's (tile, segment) table
@@ -69,6 +70,7 @@ struct Tables {
   const uint64_t* seg_lbase;   // [L]   first entry of the segment's list region in the list arrays
   const uint32_t* seg_lq;      // [L]   entries per sub-list in that region (min(kSubLists, rows) sub-lists)
   const uint32_t* seg_zc;      // [L]   top-k: 1 when the fused pass stores +0 at the candidates
+                               //       of keys from R_Z on
   const int32_t* chunk_sf;     // [nchunks] first / last segment of each data tile
   const int32_t* chunk_sl;
   const int32_t* row_seg;      // [nrows] segment of each row

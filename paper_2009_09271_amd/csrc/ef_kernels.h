@@ -1566,6 +1566,7 @@ __global__ __launch_bounds__(kSelNT) void k_sample_select(Tables T, WSel ws0, Ba
     if (sh && (span >> (sh - 1u)) < (uint32_t)kHBins - 2u) --sh;
     if (threadIdx.x == 0) {
       R[R_A] = thr;
+      R[R_Z] = thr + (top - thr) / 2u + 1u;
       R[R_IA] = 0xFFFFFFFFu;
       R[R_SH] = sh;
       R[R_MODE] = 0;
@@ -1623,13 +1624,15 @@ __device__ __forceinline__ void stream_row(const Tables& T, const void* g, const
   const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint32_t* R = res_of(ws, l);
   uint32_t mode = 1, A = 0, IA = 0, sh = 0, ulo = 0, tlast = 0;
-  bool zc = false;  // top-k, fused: +0 stored at the candidates, not acc
+  bool zc = false;           // top-k, fused: +0 stored at the candidates from key zk on, not acc
+  uint32_t zk = 0xFFFFFFFFu;
   if constexpr (KIND == 0) {
     mode = R[R_MODE];
     A = R[R_A];
     IA = R[R_IA];
     sh = R[R_SH];
     zc = ZC && FUSED && T.seg_zc[l] != 0u;
+    if (zc) zk = R[R_Z];
   } else {
     tlast = (uint32_t)(T.seg_tau[l] - 1u);  // the largest candidate key
     ulo = T.seg_ulo[l];
@@ -1715,7 +1718,7 @@ __device__ __forceinline__ void stream_row(const Tables& T, const void* g, const
         } else if (eq) {
           cm[r][q] = gt | __ballot(in(r, q) && k == A && i0[r] + q < IA);
         }
-        c = __builtin_amdgcn_inverse_ballot_w64(cm[r][q]);
+        c = k >= zk;  // (above A: a candidate)
       } else {
         c = in(r, q) && uk[r][q] <= tlast;
         cm[r][q] = __ballot(c);
@@ -1728,7 +1731,8 @@ __device__ __forceinline__ void stream_row(const Tables& T, const void* g, const
     // +0 stored at the candidates, whose losers the emission restores: random-k (the window's losers
     // are few, about 6 sqrt(k_l) + 32 of a segment; zeroing the winners afterwards instead wrote
     // single words into lines long evicted from the caches: 1e9 elements at 10 %, 1.9 of the
-    // emission's 2.3 ms) and top-k segments with seg_zc.  The exact path puts them all back first.
+    // emission's 2.3 ms) and top-k segments with seg_zc, there from the key R_Z on, where the k_l-th key
+    // is expected.  The exact path puts them all back first.
     if (FUSED && (KIND == 1 || zc)) store(r, z);
     if (lane == 0) S.wt[r * kStrW + wid] = n[r];
   }
@@ -3102,11 +3106,12 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
   const uint32_t myrow = row0 + lane;
   const bool has_row = lane < RW && myrow < (uint32_t)T.nrows;
   uint32_t cnt = 0, off = 0, Tk = 0, IT = 0, pend = 0, co = 0, in_acc = 0;
-  // rl: the pass stored +0 at this row's candidates (random-k, fused; top-k segments with seg_zc
-  // unless a candidate retry put acc back): losers get their values back, winners are left;
-  // otherwise winners get +0.  A row emitted from acc whose candidates are +0 first puts them
-  // back (rst, ocnt and oco: its own candidates).
-  uint32_t rl = 0, rst = 0, ocnt = 0, oco = 0, pbeg = 0, tb = 0;
+  // zk: the pass stored +0 at this row's candidates (random-k, fused: all, zk = 0; top-k segments with
+  // seg_zc, unless a candidate retry put acc back: those of keys from zk on): losers among them get
+  // their values back, winners among the others +0.  A row emitted from acc whose candidates are +0
+  // first puts them back (rst, ocnt and oco: its own candidates).
+  constexpr uint32_t kNoZ = 0xFFFFFFFFu;  // none (above every magnitude)
+  uint32_t zk = kNoZ, rst = 0, ocnt = 0, oco = 0, pbeg = 0, tb = 0;
   bool last_row = false;  // of its segment
   if (has_row) {
     const int l = ONE ? 0 : T.row_seg[myrow];  // one segment: no load before the record
@@ -3133,7 +3138,7 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
       in_acc = 1u;
     } else {
       co = row_entry(T, ws, myrow, cnt, co);
-      rl = zrow ? 1u : 0u;
+      if (zrow) zk = KIND == 0 ? R[R_Z] : 0u;
     }
     if (R[R_SLOW]) {
       cnt = 0;
@@ -3208,7 +3213,7 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
       const uint32_t rTk = of_row(Tk, r), rIT = of_row(IT, r);
       const uint32_t roffr = __shfl(off + done, (int)r, 64);
       // (one segment: no row's candidates are +0 where another's are not, but a row emitted from acc)
-      const uint32_t rpend = of_row(pend, r), rrl = ONE && !AR ? of_row(rl, r) : (uint32_t)__shfl(rl, (int)r, 64);
+      const uint32_t rpend = of_row(pend, r), rzk = ONE && !AR ? of_row(zk, r) : (uint32_t)__shfl(zk, (int)r, 64);
       const uint32_t rpbeg = of_row(pbeg, r);
       const bool certain = KIND == 1 && (i & kCertain);
       uint32_t ck = k;
@@ -3222,6 +3227,7 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
       const uint32_t tn = tile_of(rn);
       if (f + 64 < total) fetch(sn, tn, ian, k, i, v);
       const bool win = in && (certain || ck > rTk || (ck == rTk && ci < rIT));
+      const bool zeroed = KIND == 0 ? ck >= rzk : rzk == 0u;
       const uint64_t bw = __ballot(win);
       // this pass's lanes of row r before this lane: [lo_r, lane)
       const uint32_t lo_r = rpre > f0 ? rpre - f0 : 0u;
@@ -3230,9 +3236,9 @@ __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_
       if (win && pos - rpbeg < rpend - rpbeg) {
         out_idx[pos] = ci;
         if (out_val) out_val[pos] = cv;
-        if (e_zero && !rrl) e_zero[ci] = 0.0f;
+        if (e_zero && !zeroed) e_zero[ci] = 0.0f;
       }
-      if (e_zero && rrl && in && !win) e_zero[ci] = cv;  // a losing candidate stored as +0: its value
+      if (e_zero && zeroed && in && !win) e_zero[ci] = cv;  // a losing candidate stored as +0: its value
       // each row lane adds its winners of this pass
       if (has_row) {
         const uint32_t a = pre > f0 ? pre - f0 : 0u, z = incl > f0 ? min(incl - f0, 64u) : 0u;
@@ -3299,7 +3305,8 @@ __global__ __launch_bounds__(kNT) void k_emit_row(Tables T, WSel ws0, uint32_t* 
   } else {
     co = row_entry(T, ws, row, cnt, ws.coff[row]);
   }
-  const bool restore = zrow && !in_acc;  // losers get their values back; otherwise winners get +0
+  const bool restore = zrow && !in_acc;  // the pass stored +0 at candidates (top-k: of keys from zk on)
+  const uint32_t zk = KIND == 0 && restore ? R[R_Z] : 0xFFFFFFFFu;
   auto fetch = [&](uint32_t j0) {  // lane's candidates of kRowU chunks
 #pragma unroll
     for (uint32_t u = 0; u < kRowU; ++u) {
@@ -3343,12 +3350,13 @@ __global__ __launch_bounds__(kNT) void k_emit_row(Tables T, WSel ws0, uint32_t* 
       done += (uint32_t)__popcll(bw);
       // (a chunk's positions lie in the segment's part of the message unless its counts are wrong)
       const bool safe = at >= pbeg && off + done <= pend;
+      const bool zeroed = KIND == 0 ? k[u] >= zk : restore;
       if (safe && __builtin_amdgcn_inverse_ballot_w64(bw)) {
         out_idx[pos] = i;
         if (out_val) out_val[pos] = v[u];
-        if (e_zero && !restore) e_zero[i] = 0.0f;
+        if (e_zero && !zeroed) e_zero[i] = 0.0f;  // a winner not stored as +0
       }
-      if (restore && __builtin_amdgcn_inverse_ballot_w64(there & ~bw)) e_zero[i] = v[u];
+      if (restore && zeroed && __builtin_amdgcn_inverse_ballot_w64(there & ~bw)) e_zero[i] = v[u];  // a loser that was
     }
   }
   if (block_rows && lane == 0) {

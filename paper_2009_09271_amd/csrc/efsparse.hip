@@ -250,16 +250,19 @@ void ef_layout::build() {
         et = (double)srank[l] * dl / ns;
       }
       const uint64_t ct = dl <= kExactMax ? (uint64_t)kl : (uint64_t)std::min(dl, std::ceil(2.0 * et + 8.0 * kl + 256.0));
-      // top-k residual: +0 stored at the candidates by the pass (their losers restored by the
-      // emission) on dense sampled segments (k_l >= 0.5 % of d_l) whose candidates are not many
-      // more than the winners (under 1.8 k_l expected), else +0 stored at the winners by the
-      // emission; single words written into evicted lines cost a line read and a line write
-      // each, so whichever set is smaller is written.  On sparse or small segments the winners
-      // are few either way, and a layout with no such segment keeps the pass without the test
-      // (ResNet-50 per layer, 57.6 against 61.9 us); segments sampled whole are left out for that
-      // reason: their few winners did not pay for the test over the whole layout (ResNet-50 per
-      // layer at 1 %, whose 4096-element layers qualified: 114.1 -> 110.7 us per step)
-      zc[l] = dl > kExactMax && kl >= 0.005 * dl && et <= 1.8 * kl ? 1u : 0u;
+      // top-k residual.  Single words written into evicted lines cost a line read and a line write each, so
+      // on sampled segments that send much the pass stores +0 itself, at keys from R_Z on, the middle of
+      // where the k_l-th key is expected; the emission then writes only where that middle missed (losers
+      // above it, winners below: a few percent of k_l).  Against +0 stored at all candidates: BERT per
+      // layer at 10 % 593 -> 447 us, flat at 10 % 392 -> 378.  Segments that send less keep a pass
+      // without the test where no other segment needs it, +0 being stored at the winners by the emission.
+      // Measured without / with (BERT-size layouts, whose e does not stay in the 256 MB of cache, cross
+      // earlier): ResNet-50 per layer at 0.6 % 94.4 / 96.6 us, 1 % 99.4 / 100.4, 3 % 116.7 / 112.4; BERT
+      // per layer 0.6 % 292.8 / 299.6, 1 % 297.5 / 291.5, 3 % 362.8 / 341.1.  Candidates under 1.8 k_l
+      // (large samples): from 0.5 % on.  Segments sampled whole have few winners either way (ResNet-50 per
+      // layer at 1 %, whose 4096-element layers would qualify: 110.7 / 114.1).
+      const double dense = (double)off64[n] > 67108864.0 ? 0.009 : 0.015;
+      zc[l] = dl > kExactMax && (kl >= dense * dl || (kl >= 0.005 * dl && et <= 1.8 * kl)) ? 1u : 0u;
       const double mu = (double)tau[l] / 4294967296.0 * dl;
       const uint64_t cr = (uint64_t)std::min(dl, std::ceil(mu + 8.0 * std::sqrt(mu) + 64.0));
       // slots: mu + 4 sqrt(mu) + 32 for top-k's mean mu per row (its candidates above the sampled

@@ -66,6 +66,27 @@ def test_randk_select_forms(d, density):
     certify_randk(acc, c.offs, c.ks, host(idx), host(val), host(e), 77 + d, 3)
 
 
+# top-k, a layout of several segments: +0 stored by the pass or by the emission (the densities on both
+# sides of the rule), segments sampled whole among them
+@pytest.mark.parametrize("density", [0.004, 0.0145, 0.0155, 0.3])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_topk_residual_store(density, dtype):
+    announce("top-k residual store", density, dtype)
+    offs = np.cumsum([0, 4096 * 40 + 3, 5, 4096 * 9, 100000, 4096 * 3 + 1]).tolist()
+    rng = np.random.default_rng(int(density * 1e4))
+    g = rng.standard_normal(offs[-1], dtype=np.float32)
+    g[offs[3]:offs[4]] = rng.integers(1, 4, offs[4] - offs[3])  # few magnitudes: ties at the threshold
+    if dtype == "bf16":
+        g16 = to_bf16_bits(g)
+        g = (g16.astype(np.uint32) << 16).view(np.float32)
+    import torch
+    c = Case(offs, density)
+    e0 = rng.standard_normal(offs[-1], dtype=np.float32)
+    e = torch.from_numpy(e0.copy()).cuda()
+    idx, val, ws = c.step("topk", g16 if dtype == "bf16" else g, e)
+    certify_topk(g + e0, c.offs, c.ks, host(idx), host(val), host(e))
+
+
 # top-k candidates of 1 to 4096 a row, spread over rows of every kind (a wavefront's chunks of 64, the
 # static slot and the overflow pool, histogram in LDS or not, the last bin), with equal magnitudes
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
