@@ -25,8 +25,8 @@
 //                    scans (a list too long for that: k_rowcount counts again, k_rowtie
 //                    resolves ties at the threshold).
 //   k_emit           per row: the winners in index order to the message and e = +0 there (where
-//                    the pass already stored +0 at every candidate, random-k and dense top-k
-//                    segments, the losing candidates get their values back instead).
+//                    the pass already stored +0, at every candidate of random-k and at the
+//                    keys from R_Z on of dense top-k segments, losers get their values back).
 // A top-k segment with fewer than k_l candidates, or whose candidates do not fit the workspace, is
 // collected again at a lower threshold (k_resolve sets it, k_collect re-reads the rows); only if
 // that falls short too, or for random-k, is it resolved exactly over all of its elements by
@@ -2618,7 +2618,7 @@ __global__ __launch_bounds__(kSelNT, SMALL ? 8 : 4) void k_select(Tables T, WSel
       if (slow) atomicOr(ws.diag, kDiagSlowPath);
     }
   }
-  // The streaming pass stored +0 at every candidate (random-k; top-k segments with seg_zc): the
+  // The streaming pass stored +0 at candidates (random-k: all; top-k segments with seg_zc): the
   // exact path needs acc there, which the candidates keep (a row whose candidates did not fit
   // stored acc there itself).  Uniform.
   auto restore_candidates = [&]() {
