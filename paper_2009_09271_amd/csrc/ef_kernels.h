@@ -2087,7 +2087,7 @@ __device__ __forceinline__ void collect_retry(const Tables& T, const WSel& ws, c
 }
 
 constexpr uint32_t kCollectBuf = 512;  // listed candidates a wavefront of k_collect stages in LDS
-// Chunks of 64 candidates loaded together: four where a wavefront has one row (BERT flat at 10 %, 480
+// Chunks of 64 candidates loaded together: four where a wavefront has one row (BERT flat at 10 %, over 400
 // candidates a row: 24.8 -> 20.9 us), one in a batch (16 workers on ResNet-50: 27.7 us, 28.4 with four).
 constexpr uint32_t collect_chunks(uint32_t rows) { return rows == 1u ? 4u : 1u; }
 
