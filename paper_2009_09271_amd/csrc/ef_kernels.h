@@ -484,17 +484,21 @@ __device__ __forceinline__ float column_sum(const float* v, int32_t W, int32_t K
 // j's thread also writes sums[j], the column sum of the rows in worker order.
 // Entry j starts the tiles after its predecessor's tile, up to its own (past the last entry the
 // tiles up to nt start at K).  A short run of tiles is written by its entry's thread; a longer one
-// (a gap in a message crowded into a few layers) by a wavefront as one coalesced run, after each
-// round (a thread writes its long run itself if the workgroup's list of them is full).  The
-// workgroup's four wavefronts take the long runs in turn: by the whole workgroup one after another
-// the pass took 11.6 us over 16 top-k messages of ResNet-50's d whose gaps are hundreds of tiles,
-// now 8.3 us.
+// (a gap in a message crowded into a few layers) as one coalesced run, after each round (a thread
+// writes its long run itself if the workgroup's list of them is full).  Runs of up to kRunWave
+// tiles are taken in turn by the workgroup's four wavefronts: 16 messages over 1.1e8 elements with
+// gaps of 40 / 600 / 2000 tiles take 12.0 / 10.9 / 11.2 us, by the whole workgroup one run after
+// another 17.0 / 13.2 / 13.4.  Longer ones, of which a workgroup seldom has four, are written by the
+// whole workgroup: 4 messages over 1e9 elements with gaps of 40,000 tiles 66 us (all the entries in
+// the first hundredth of 1.1e8 elements: 9 us, by one wavefront 31).
 // For ascending messages the entries' runs partition 0..nt.
 constexpr uint32_t kRunOwn = 32;        // runs of at most this many tiles are written by their own thread
                                         // (ResNet-50 top-k messages: 8.2 us with 128, 5.0 with 16-64)
 constexpr int kRangeUBig = 8;           // entries per thread per round for long messages
 constexpr int64_t kRangeBig = 1 << 22;  // total entries (W K) from which the long form is used
 constexpr uint32_t kRangeStash = 512;   // long runs listed per workgroup and round
+constexpr uint32_t kRunWave = 4096;     // long runs of up to this many tiles are written by one wavefront
+                                        // (gaps of 4000 tiles, 4 messages over 1e9: 19.8 us, by four 23)
 
 template <int kRangeU>
 __global__ __launch_bounds__(kNT) void k_agg_ranges(int32_t d, int32_t K, int32_t nt, const uint32_t* idx,
@@ -507,10 +511,9 @@ __global__ __launch_bounds__(kNT) void k_agg_ranges(int32_t d, int32_t K, int32_
   uint32_t* ts = tile_start + (size_t)w * ts_stride;
   const size_t tbase = (size_t)w * ts_stride;
   auto tile = [&](uint32_t i) -> uint32_t { return i < (uint32_t)d ? i / kAggTile : (uint32_t)nt; };
-  // tile tau of entry e's run starts at e, except past the last entry's own tile (at K)
-  auto value = [&](uint32_t e, uint32_t tau, uint32_t e_own) -> uint32_t {
-    return e == (uint32_t)K - 1u && tau > e_own ? (uint32_t)K : e;
-  };
+  // tile tau of entry e's run starts at e, except past the last entry's own tile (at K); the other
+  // entries' runs end at their own tiles
+  auto value = [&](uint32_t e, uint32_t tau, uint32_t e_own) -> uint32_t { return tau > e_own ? (uint32_t)K : e; };
   if (threadIdx.x == 0) s_nlong = 0;
   __syncthreads();
   const uint32_t round = gridDim.x * (uint32_t)kNT * (uint32_t)kRangeU;
@@ -565,18 +568,24 @@ __global__ __launch_bounds__(kNT) void k_agg_ranges(int32_t d, int32_t K, int32_
     }
     __syncthreads();
     const uint32_t nl = min(s_nlong, kRangeStash);
-    for (uint32_t q = threadIdx.x / 64u; q < nl; q += kNT / 64u) {
+    // run q by the threads t of NT
+    auto write = [&](uint32_t q, uint32_t t, auto nth) {
+      constexpr uint32_t NT = decltype(nth)::value;
       const uint32_t qa = s_ta[q], qe = qa + s_n[q], qj = s_j[q], qown = s_own[q];
       // 16-byte stores over the part of the run aligned in memory, single words at its two ends
       const uint32_t a4 = min(qe, qa + (uint32_t)((4u - (tbase + qa) % 4u) % 4u));
       const uint32_t b4 = a4 + (qe - a4) / 4u * 4u;
-      if (lane < a4 - qa) ts[qa + lane] = value(qj, qa + lane, qown);
-      if (lane < qe - b4) ts[b4 + lane] = value(qj, b4 + lane, qown);
-      for (uint32_t o = a4 + 4u * lane; o < b4; o += 4u * 64u) {
+      if (t < a4 - qa) ts[qa + t] = value(qj, qa + t, qown);
+      if (t < qe - b4) ts[b4 + t] = value(qj, b4 + t, qown);
+      for (uint32_t o = a4 + 4u * t; o < b4; o += 4u * NT) {
         const uint4 v = make_uint4(value(qj, o, qown), value(qj, o + 1, qown), value(qj, o + 2, qown),
                                    value(qj, o + 3, qown));
         *reinterpret_cast<uint4*>(ts + o) = v;
       }
+    };
+    for (uint32_t q = 0; q < nl; ++q) {
+      if (s_n[q] > kRunWave) write(q, threadIdx.x, std::integral_constant<uint32_t, kNT>{});
+      else if (q % (kNT / 64u) == threadIdx.x / 64u) write(q, lane, std::integral_constant<uint32_t, 64>{});
     }
     __syncthreads();
     if (threadIdx.x == 0) s_nlong = 0;

@@ -47,6 +47,34 @@ def test_sparse_aggregate_tile_entries(counts):
         assert_f32_equal(out, O.decompress_aggregate_sparse(d, idx, val, average), f"average={average}")
 
 
+# gaps between a message's entries, in tiles of 1024 elements: the last written by its entry's thread, by one
+# wavefront and the first of each longer form, up to the last tile and past it; three messages whose range
+# tables start at different places modulo 16 bytes
+@pytest.mark.parametrize("last", [1, 33, 4096, 4097])
+def test_sparse_aggregate_long_gaps(last):
+    import paper_2009_09271_amd as E
+    import torch
+    announce("sparse aggregate gaps", last)
+    gaps = [31, 32, 33, 34, 4095, 4096, 4097, 4098, 1]
+    W, tiles = 3, sum(gaps) + last
+    d = 1024 * tiles - 5
+    assert (tiles + 1) % 4 != 0  # (tables of tiles + 1 words)
+    rng = np.random.default_rng(last)
+    idx = []
+    for w in range(W):
+        at = np.cumsum(rng.permutation(gaps)) - (w == 0)  # the tiles that hold entries
+        idx.append(np.sort(np.concatenate([1024 * t + rng.choice(1000, 3, replace=False) for t in at])))
+    idx = np.stack(idx).astype(np.uint32)
+    K = idx.shape[1]
+    val = rng.standard_normal((W, K)).astype(np.float32)
+    c = Case([0, d], (K + 0.25) / d)
+    assert c.K == K
+    out = torch.empty(d, dtype=torch.float32, device="cuda")
+    E.decompress_aggregate(c.L, E.EF_MSG_SPARSE, W, dev(idx.view(np.int32)), dev(val), out,
+                           c.L.workspace(E.EF_OP_AGG_SPARSE, W))
+    assert_f32_equal(out, O.decompress_aggregate_sparse(d, idx, val, True), f"gap to the end {last}")
+
+
 # random-k on one segment: the last row count and the last window of the select kernel's small form and
 # of direct lists, the first of each larger form, and a list in global memory with the rows' offsets from
 # one block of rows and from several; one row, several and the most to a collecting wavefront
