@@ -747,23 +747,28 @@ __device__ __forceinline__ void agg_add_rest(AggLds& S, int nw, int w0, int32_t 
 }
 
 // Tiles whose workers hold more than this many entries each on average add them worker by worker
-// (agg_add_workers; BERT's d, 16 workers at 10 %: 316 us; at 1 %, about 10 entries per worker and
+// (agg_add_workers; BERT's d, 16 workers at 10 %: 310 us; at 1 %, about 10 entries per worker and
 // tile, the loads of one worker at a time leave five lanes in six idle and the staged form is
 // faster; 12, 16 and 24 in place of 48 measured the same within 1 % at 1, 3 and 10 %).
 constexpr uint32_t kAggDense = 48;
-constexpr int kAggW = 16;  // dense tiles: chunks of 64 entries loaded together
-constexpr int kAggJoint = 4;  // ... of which this many, if one worker's, are added together
+// Dense tiles: chunks of 64 entries loaded together.  Sixteen hide the latency of the tiles that a
+// sparse message crowds into (top-k messages of ResNet-50 at 1 %, 16 workers: 38 us, with four 42).
+// Where every tile is so full, 16 in flight in each of a chip's wavefronts are more than the L2s hold,
+// and lines that two chunks share are fetched twice: messages of over a quarter of the elements load
+// four (BERT's d at 30 %, 16 workers: 859 us with sixteen, 803 with four; at 10 % 310 with either).
+constexpr int kAggW = 16, kAggWFull = 4;
 
 // Dense tiles: the group's workers one after another, in order.  A message holds each position at
 // most once, so the adds of one worker never collide: a chunk of up to 64 of one worker's entries
 // is added by its lanes at once, with no claims and no barriers (the one wavefront's LDS accesses
 // take effect in program order, so a position's adds run in worker order).  The chunks (worker by
-// worker, 64 entries each) are numbered through a prefix over the workers' chunk counts; kAggW
-// chunks are loaded together (coalesced), then added in order.  What bounds a dense tile is the
-// chain of LDS round trips: where kAggJoint chunks in a row are one worker's, their sums are read
-// together, added and written together (BERT's d, 16 workers at 10 %: 400 -> 316 us; ResNet-18's
-// d, 8 workers' top-k messages at 10 %: 30 -> 22 us).  (LDS float atomics, which would return
-// nothing to wait for, took 911 us there: they are processed a lane at a time.)
+// worker, 64 entries each) are numbered through a prefix over the workers' chunk counts; AW chunks
+// are loaded together (coalesced), then added in order.  A lane without an entry gets an index past
+// the tile as its load's alternative (cleared by a second test after the loads, BERT's d at 10 %, 16
+// workers: 387 us).  (Reading four chunks' sums together measured the same as one after another; LDS
+// float atomics, which would return nothing to wait for, took 911 us there: they are processed a lane
+// at a time.)
+template <int AW>
 __device__ __forceinline__ void agg_add_workers(AggLds& S, int nw, int w0, int32_t K, const uint32_t* idx,
                                                 const float* val, uint32_t lo, uint32_t hi) {
   const uint32_t lane = threadIdx.x;
@@ -772,12 +777,11 @@ __device__ __forceinline__ void agg_add_workers(AggLds& S, int nw, int w0, int32
   const uint32_t ch = (n + 63u) / 64u, chi = wave_incl_scan(ch);
   const uint32_t cpre = chi - ch;  // first chunk of worker `lane`
   const uint32_t nch = __shfl(chi, 63, 64);
-  for (uint32_t q0 = 0; q0 < nch; q0 += kAggW) {
-    uint32_t ci[kAggW];
-    float cv[kAggW];
-    int cw[kAggW];
+  for (uint32_t q0 = 0; q0 < nch; q0 += AW) {
+    uint32_t ci[AW];
+    float cv[AW];
 #pragma unroll
-    for (int u = 0; u < kAggW; ++u) {
+    for (int u = 0; u < AW; ++u) {
       const uint32_t q = q0 + (uint32_t)u;
       // chunk q's worker: the last one whose chunks start at or before q (wave-uniform)
       const int w = (int)__popcll(__ballot(lane < (uint32_t)nw && cpre <= q)) - 1;
@@ -786,29 +790,19 @@ __device__ __forceinline__ void agg_add_workers(AggLds& S, int nw, int w0, int32
       const size_t j = (size_t)(w0 + w) * K + (uint32_t)__builtin_amdgcn_readlane((int)a, w) + f;
       ci[u] = ok ? idx[j] : hi;  // hi: adds nothing below
       cv[u] = ok ? val[j] : 0.0f;
-      cw[u] = w;
     }
-    // Four chunks of one worker (their positions differ): their sums are read together, not one
-    // after another's write.
 #pragma unroll
-    for (int u = 0; u < kAggW; u += kAggJoint) {
-      if (cw[u] == cw[u + kAggJoint - 1]) {
-        float t[kAggJoint];
-#pragma unroll
-        for (int v = 0; v < kAggJoint; ++v) {
-          const uint32_t x = ci[u + v] - lo;
-          t[v] = S.acc[x < kAggTile ? x : 0u];
-        }
-#pragma unroll
-        for (int v = 0; v < kAggJoint; ++v)
-          if (ci[u + v] >= lo && ci[u + v] < hi) S.acc[ci[u + v] - lo] = t[v] + cv[u + v];
-      } else {
-#pragma unroll
-        for (int v = u; v < u + kAggJoint; ++v)
-          if (ci[v] >= lo && ci[v] < hi) S.acc[ci[v] - lo] += cv[v];
-      }
-    }
+    for (int u = 0; u < AW; ++u)
+      if (ci[u] >= lo && ci[u] < hi) S.acc[ci[u] - lo] += cv[u];
   }
+}
+
+// Adds a worker group's E entries by the form that suits their number.
+__device__ __forceinline__ void agg_add_group(AggLds& S, int nw, int w0, int32_t d, int32_t K, const uint32_t* idx,
+                                              const float* val, uint32_t lo, uint32_t hi, uint32_t E) {
+  if (E <= kAggDense * (uint32_t)nw) agg_add_rest(S, nw, w0, K, idx, val, lo, hi, 0u, E);
+  else if ((uint32_t)K > (uint32_t)d / 4u) agg_add_workers<kAggWFull>(S, nw, w0, K, idx, val, lo, hi);
+  else agg_add_workers<kAggW>(S, nw, w0, K, idx, val, lo, hi);
 }
 
 // Workgroup b -> tile: workgroups are dispatched to the 8 XCDs in turn (b mod 8), so XCD x is
@@ -870,14 +864,12 @@ __global__ __launch_bounds__(64) void k_agg_sparse(int32_t d, int32_t W, int32_t
     *reinterpret_cast<f4*>(&S.acc[(r * 64 + lane) * 4]) = z;
   }
   __syncthreads();
-  if (E > kAggDense * (uint32_t)nw0) agg_add_workers(S, nw0, 0, K, idx, val, lo, hi);
-  else agg_add_rest(S, nw0, 0, K, idx, val, lo, hi, 0u, E);
+  agg_add_group(S, nw0, 0, d, K, idx, val, lo, hi, E);
   for (int w0 = 64; w0 < W; w0 += 64) {  // further worker groups
     const int nw = min(64, W - w0);
     const uint32_t* tg = tile_start + (size_t)(w0 + min(lane, nw - 1)) * (nt + 1) + t;
     const uint32_t Eg = agg_group(S, nw, K, tg[0], tg[1]);
-    if (Eg > kAggDense * (uint32_t)nw) agg_add_workers(S, nw, w0, K, idx, val, lo, hi);
-    else agg_add_rest(S, nw, w0, K, idx, val, lo, hi, 0u, Eg);
+    agg_add_group(S, nw, w0, d, K, idx, val, lo, hi, Eg);
   }
   __syncthreads();
 #pragma unroll

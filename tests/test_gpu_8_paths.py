@@ -75,6 +75,33 @@ def test_sparse_aggregate_long_gaps(last):
     assert_f32_equal(out, O.decompress_aggregate_sparse(d, idx, val, True), f"gap to the end {last}")
 
 
+# messages of a quarter of the elements and one entry more (chunks loaded by fours), tiles of 1 to 1024 entries
+# of each worker among them, and more workers than one group holds
+@pytest.mark.parametrize("W", [1, 5, 67])
+@pytest.mark.parametrize("over", [0, 1])
+def test_sparse_aggregate_full_messages(W, over):
+    import paper_2009_09271_amd as E
+    import torch
+    d = 1024 * 9 + 200
+    K = d // 4 + over
+    assert (K > d // 4) == bool(over)
+    announce("sparse aggregate full messages", W, K)
+    rng = np.random.default_rng(W + over)
+    idx = []
+    for w in range(W):  # one tile sent whole, one entry in another, the rest at random
+        whole, single = 1024 * (w % 7), 1024 * 8 + w % 200
+        rest = np.setdiff1d(np.arange(d), np.r_[whole:whole + 1024, 1024 * 8:1024 * 9])
+        idx.append(np.sort(np.r_[whole:whole + 1024, single, rng.choice(rest, K - 1025, replace=False)]))
+    idx = np.stack(idx).astype(np.uint32)
+    val = (rng.standard_normal((W, K)) * 10.0 ** rng.uniform(-3, 3, (W, K))).astype(np.float32)
+    c = Case([0, d], (K + 0.25) / d)
+    assert c.K == K
+    out = torch.empty(d, dtype=torch.float32, device="cuda")
+    E.decompress_aggregate(c.L, E.EF_MSG_SPARSE, W, dev(idx.view(np.int32)), dev(val), out,
+                           c.L.workspace(E.EF_OP_AGG_SPARSE, W))
+    assert_f32_equal(out, O.decompress_aggregate_sparse(d, idx, val, True), f"{W} workers, {K} entries")
+
+
 # random-k on one segment: the last row count and the last window of the select kernel's small form and
 # of direct lists, the first of each larger form, and a list in global memory with the rows' offsets from
 # one block of rows and from several; one row, several and the most to a collecting wavefront
