@@ -2485,11 +2485,16 @@ __device__ __forceinline__ bool band_threshold(const SubLists& lk, const SubList
 // beside the winners, so that counting every row's winners again, 22 us on BERT flat at 10 % and 55 us
 // on 1e9 elements at 1 %, is not needed); k_rowsum turns the counts into offsets over many workgroups.
 // SMALL: segments of at most kSmallRows rows, random-k on direct layouts only, lists expected to fit
-// kSmallList entries; two of its workgroups fit a CU (8 workers' random-k steps on ResNet-18's 62
-// layers, 496 workgroups: 24.7 -> 20.7 us).
+// kSmallList entries.  PAIR: 64 registers a thread, so that two workgroups fit a CU (8 workers' random-k
+// steps on ResNet-18's 62 layers, 496 workgroups: 24.7 -> 20.7 us).  Random-k spills 32 registers there;
+// launches that give no CU a second workgroup (kCUs) take the form without PAIR, 87 registers and no
+// spill.  Steps with PAIR / without: random-k per layer at 1 %, ResNet-50's 161 workgroups 72.8 / 66.6 us,
+// ResNet-18's 62 43.0 / 40.0, 4 workers' 248 127.8 / 120.4; 5 workers' 310, with the larger form's one
+// workgroup to a CU, 156.9 / 157.8.  Top-k spills nothing with PAIR and measures the same.
 constexpr uint32_t kSmallList = 4096, kSmallRows = 4096;
-template <int KIND, bool BIG, bool SMALL = false>
-__global__ __launch_bounds__(kSelNT, SMALL ? 8 : 4) void k_select(Tables T, WSel ws0, uint32_t* out_idx, float* out_val,
+constexpr uint32_t kCUs = 256;
+template <int KIND, bool BIG, bool SMALL = false, bool PAIR = false>
+__global__ __launch_bounds__(kSelNT, PAIR ? 8 : 4) void k_select(Tables T, WSel ws0, uint32_t* out_idx, float* out_val,
                                                    uint32_t step, Batch BT) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
   float* e_zero = BT.e[blockIdx.y];

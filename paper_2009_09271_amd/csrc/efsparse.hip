@@ -705,8 +705,10 @@ int run_select(const ef_layout* L, const Steps& P, unsigned phases, void* stream
       const uint32_t per = kRowsumT * kRowBlocks;
       brows = kRowsumT * (uint32_t)(((uint32_t)L->nrows + per - 1) / per);
       EF_LAUNCH(k_rowsum<KIND>, dim3(((unsigned)L->nrows + brows - 1) / brows, nw), blk, 0, st, T, w, bt, brows);
+    } else if (KIND == 1 && L->sel_small[KIND] && (uint64_t)L->L * nw <= kCUs) {
+      EF_LAUNCH((k_select<KIND, false, KIND == 1>), sgrid, sblk, 0, st, T, w, idx, val, P.step, bt);
     } else if (L->sel_small[KIND]) {
-      EF_LAUNCH((k_select<KIND, false, true>), sgrid, sblk, 0, st, T, w, idx, val, P.step, bt);
+      EF_LAUNCH((k_select<KIND, false, true, true>), sgrid, sblk, 0, st, T, w, idx, val, P.step, bt);
     } else {
       EF_LAUNCH((k_select<KIND, false>), sgrid, sblk, 0, st, T, w, idx, val, P.step, bt);
     }

@@ -166,3 +166,24 @@ def test_topk_crowded_rows(d, density, dtype):
     assert c.L.diag(ws, E.EF_OP_TOPK) & 4 == 0
     certify_topk(g, c.offs, c.ks, host(idx), host(val), host(e))
 
+
+
+# random-k in one batch: 256 select workgroups (one to a CU) and more (two to a CU), segments of one to 41 rows
+@pytest.mark.parametrize("W", [16, 17])
+def test_randk_batch_workgroups(W):
+    import paper_2009_09271_amd as E
+    import torch
+    announce("random-k batch workgroups", W)
+    offs = np.cumsum([0, 4096 * 40 + 3, 5, 4096, 70001, 1, 300] + [4097] * 10).tolist()
+    c = Case(offs, 0.03)
+    assert len(c.ks) == 16
+    rng = np.random.default_rng(W)
+    g = (rng.standard_normal((W, c.d), dtype=np.float32) + np.float32(0.0))
+    gd, e = dev(g), torch.zeros((W, c.d), dtype=torch.float32, device="cuda")
+    idx = torch.empty((W, c.K), dtype=torch.int32, device="cuda")
+    val = torch.empty((W, c.K), dtype=torch.float32, device="cuda")
+    ws, stride = E.batch_workspace(c.L, E.EF_OP_RANDK, W)
+    seeds = [1000 + w for w in range(W)]
+    E.ef_step_randk_batch(c.L, list(gd), list(e), seeds, 5, idx, val, ws, stride)
+    for w in range(W):
+        certify_randk(g[w], c.offs, c.ks, host(idx[w]), host(val[w]), host(e[w]), seeds[w], 5, f"worker {w}")
