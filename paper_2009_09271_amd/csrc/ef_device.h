@@ -17,7 +17,8 @@ constexpr uint32_t kTile = 4096;              // data elements per tile (the row
 constexpr int kHBins = 2048;                  // LDS histogram bins (11 bits per radix level)
 constexpr int kResWords = 16;                // per-segment selection record (uint32 words)
 constexpr int kSubLists = 16;                // a segment's list of undecided candidates is kept as 16
-                                              // sub-lists (row r appends to sub-list r % 16)
+                                              // sub-lists (row r appends to sub-list r % 16, random-k's
+                                              // long segments by collecting wavefronts)
 constexpr int kExactMax = 4096;               // top-k: segments up to this size are sampled whole (exact rule)
 constexpr int kSampleRun = 256;               // samples per sample run (one workgroup each)
 constexpr int kSampleTotal = 16384;           // top-k: samples shared by a layout's sampled segments

@@ -280,15 +280,23 @@ void ef_layout::build() {
       etsum += dl <= kExactMax ? kl : std::min(dl, et);
       bt += ct;
       br += cr;
-      // lists: sub-list c takes the entries of the segment's rows c, c + 16, ...; each of the
-      // min(16, rows) sub-lists in use holds the segment's bound (up to 16 rows: one row each, at
-      // most a tile) or an eighth of it, at most the elements of its rows; a sub-list that
-      // overflows sends the segment to the exact path
-      // (scaled by the pool knob)
+      // lists: row r of a segment appends to sub-list r % 16.  Each of the min(16, rows) sub-lists in
+      // use holds the segment's bound (up to 16 rows: one row each, at most a tile) or an eighth of it,
+      // at most the elements of its rows; a sub-list that overflows sends the segment to the exact path
+      // (scaled by the pool knob).  In random-k's segments of kCollectWide rows and more a collecting
+      // wavefront's up to 64 rows append to sub-list wavefront % 16 together (those of a wavefront that
+      // also has another segment's rows to r % 16): more rows than a sixteenth, but of n wavefronts at
+      // most 64 * ceil(n / 16), from 1024 rows on an eighth of the rows.  An eighth of the undecided
+      // keys therefore fits as well.
       const uint64_t bl = std::max(ct, cr), nr = (uint64_t)(cbase[l + 1] - cbase[l]);
       const uint64_t rows_cap = (nr + kSubLists - 1) / kSubLists * kTile;
       const uint64_t q0 = nr <= kSubLists ? std::min<uint64_t>(bl, kTile) : std::min<uint64_t>(bl, (bl + 7) / 8 + 64);
-      const uint64_t q = std::min<uint64_t>(rows_cap, (uint64_t)std::ceil((double)q0 * pool));
+      uint64_t q = std::min<uint64_t>(rows_cap, (uint64_t)std::ceil((double)q0 * pool));
+      if (nr >= kCollectWide) {
+        const double und = (double)(tau[l] - ulo[l]) / 4294967296.0 * dl;
+        const double most = std::min(dl, std::ceil(und + 8.0 * std::sqrt(und) + 64.0));
+        q = std::max(q, (uint64_t)std::ceil((std::ceil(most / 8.0) + 64.0) * std::min(pool, 1.0)));
+      }
       lbase[l] = lsum;
       lq[l] = (uint32_t)q;
       lsum += q * std::min<uint64_t>(nr, kSubLists);

@@ -4,7 +4,7 @@ Bit-exact against the CPU oracle, through the C ABI."""
 import numpy as np
 import pytest
 
-from efs_gpu import Case, announce, assert_f32_equal, certify_randk, certify_topk, dev, host
+from efs_gpu import Case, announce, assert_f32_equal, certify_randk, certify_topk, dev, host, order_certificate
 from oracle import efsparse_oracle as O
 from workloads.generate import to_bf16_bits
 
@@ -102,6 +102,17 @@ def test_sparse_aggregate_full_messages(W, over):
     assert_f32_equal(out, O.decompress_aggregate_sparse(d, idx, val, True), f"{W} workers, {K} entries")
 
 
+def _certify_long_segment(c, before, acc, idx, val, e, seed, step):
+    """One long segment after `before` segments of one element each and before more of them."""
+    idx, n, k = host(idx).view(np.uint32).astype(np.int64), c.offs[before + 1] - before, c.ks[before]
+    assert_f32_equal(val, acc[idx], "values")
+    want = acc.copy()
+    want[idx] = 0.0
+    assert_f32_equal(e, want, "residual")
+    assert np.array_equal(np.r_[idx[:before], idx[before + k:]], np.r_[np.arange(before), np.arange(before + n, c.d)])
+    order_certificate(idx[before:before + k] - before, n, k, lambda a, b: ~O.randk_keys(n, before, seed, step, a, b), "long segment")
+
+
 # random-k on one segment: the last row count and the last window of the select kernel's small form and
 # of direct lists, the first of each larger form, and a list in global memory with the rows' offsets from
 # one block of rows and from several; one row, several and the most to a collecting wavefront
@@ -119,6 +130,23 @@ def test_randk_select_forms(d, density):
     idx, val, ws = c.step("randk", acc, e, seed=77 + d, step=3)
     assert c.L.diag(ws, E.EF_OP_RANDK) == 0
     certify_randk(acc, c.offs, c.ks, host(idx), host(val), host(e), 77 + d, 3)
+
+
+# random-k with every element undecided: 1088 rows whose 17 collecting wavefronts of 64 rows list them by
+# wavefront, two in one sub-list, between segments of one element (which make the rows so many)
+def test_randk_wide_lists_hold_two_wavefronts():
+    import paper_2009_09271_amd as E
+    import torch
+    announce("random-k wide lists")
+    before, n, nrows = 4096 * 5, 4096 * 1088, 131072
+    offs = np.r_[np.arange(before + 1), before + n + np.arange(nrows - before - 1088 + 1)].tolist()
+    c = Case(offs, 0.2, tune={E.EF_TUNE_RANDK_EXTRA: 1e9})
+    rng = np.random.default_rng(3)
+    acc = rng.standard_normal(c.d, dtype=np.float32) + np.float32(0.0)
+    e = torch.zeros(c.d, dtype=torch.float32, device="cuda")
+    idx, val, ws = c.step("randk", acc, e, seed=9, step=1)
+    assert c.L.diag(ws, E.EF_OP_RANDK) == 0
+    _certify_long_segment(c, before, acc, idx, val, e, 9, 1)
 
 
 # top-k, a layout of several segments: +0 stored by the pass or by the emission (the densities on both
