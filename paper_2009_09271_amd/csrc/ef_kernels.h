@@ -823,7 +823,9 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n) {
 
 // UPD: with the parameter update.  A whole tile's parameters and momentum are then loaded along with
 // the ranges, so that the update waits for no third round trip at the end (8 workers at 1 % on
-// ResNet-18's d with momentum: 42.7 -> 34.8 us; 187 MB at least, 29 us).
+// ResNet-18's d with momentum: 42.7 -> 34.8 us; 187 MB at least, 29 us).  Where many workers' messages
+// hold several entries per element the wait is short beside the adds and the registers cost up to 4 %
+// (2.56e7 elements at 40 %, 16 workers: 402 us, loaded last 389; 2 workers 105 / 114, with momentum).
 template <bool UPD>
 __global__ __launch_bounds__(64) void k_agg_sparse(int32_t d, int32_t W, int32_t K, int32_t nt,
                                                    const uint32_t* idx, const float* val,
@@ -1992,14 +1994,6 @@ __global__ __launch_bounds__(kSelNT) void k_resolve(Tables T, WSel ws0, Batch BT
   }
 }
 
-// Per row: candidates certain to win are counted; the undecided ones go to the segment's list (in
-// any order: the selection over the list does not depend on it; row r appends to sub-list
-// r % kSubLists, which spreads the atomics on the list counters).  Top-k: above / inside bin B of
-// a histogrammed segment.  Random-k: Philox key below ulo_l / in [ulo_l, tau_l).
-// One wavefront per CR consecutive rows (CR = 1 for one or a few workers, where the rows are the
-// whole grid; more per wavefront for a batch): the rows' segments, candidate counts and first 64
-// candidate keys are loaded together; counts and list positions come from ballots, and each chunk
-// of 64 candidates reserves its list space with one atomic.
 // Top-k candidate retry, one wavefront per row: the row's keys are read again from acc and every
 // key > A2 becomes a candidate, in index order, in the row's static slot or, if more, in entries
 // reserved in the overflow pool; those >= A (the first candidates) are certain winners, those in
@@ -2093,6 +2087,12 @@ constexpr uint32_t kCollectBuf = 512;  // listed candidates a wavefront of k_col
 // candidates a row: 24.8 -> 20.9 us), one in a batch (16 workers on ResNet-50: 27.7 us, 28.4 with four).
 constexpr uint32_t collect_chunks(uint32_t rows) { return rows == 1u ? 4u : 1u; }
 
+// Top-k, per row: candidates certain to win (above bin B of a histogrammed segment) are counted, the
+// undecided ones (inside it) go to the segment's list, in any order: the selection over the list does
+// not depend on it; row r appends to sub-list r % kSubLists, which spreads the atomics on the list
+// counters.  One wavefront per kCollectRows rows: their segments, candidate counts and, of one
+// segment, first candidates are loaded together; counts come from ballots, and the listed candidates
+// are staged in LDS.
 template <uint32_t kCollectRows>
 __global__ __launch_bounds__(kNT) void k_collect(Tables T, WSel ws0, Batch BT) {
   const WSel ws = ws_at(ws0, (uint64_t)blockIdx.y * BT.ws);
@@ -3094,10 +3094,11 @@ __device__ __forceinline__ uint32_t rows_before(const WSel& ws, uint32_t b) {
 // serves its rows in one or a few passes of 64 candidates, the next pass's loads in flight while
 // the current one is written.  A winner's position is its row's offset plus the row's winners
 // before it: earlier passes (kept by the row's lane) and a ballot count over the row's lanes in
-// this pass.  RW = 16 for random-k (a few candidates per row); for top-k, whose rows in the layers
-// of largest magnitude hold hundreds, 1 for one or a few workers and 4 for a batch.  A top-k row
-// with winning ties (flagged kAccRow) takes its elements in acc as its candidates.  The step's
-// last kernel, it also clears the overflow pool's counters for the next step.
+// this pass.  RW = 2 to 16 for random-k, by the candidates of a row; for top-k, whose rows in the
+// layers of largest magnitude hold hundreds, 2 for a batch and 4 on a very large sparse layout (one row
+// to a wavefront: k_emit_row).  A top-k row with winning ties (flagged kAccRow) takes its elements in
+// acc as its candidates.  The step's last kernel, it also clears the overflow pool's counters for the
+// next step.
 template <int KIND, uint32_t RW, bool ONE>
 __global__ __launch_bounds__(kNT) void k_emit(Tables T, WSel ws0, uint32_t* out_idx, float* out_val, Batch BT,
                                               int cand_zeroed, uint32_t block_rows) {

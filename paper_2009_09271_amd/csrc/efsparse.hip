@@ -256,10 +256,13 @@ void ef_layout::build() {
       // above it, winners below: a few percent of k_l).  Against +0 stored at all candidates: BERT per
       // layer at 10 % 593 -> 447 us, flat at 10 % 392 -> 378.  Segments that send less keep a pass
       // without the test where no other segment needs it, +0 being stored at the winners by the emission.
-      // Measured without / with (BERT-size layouts, whose e does not stay in the 256 MB of cache, cross
-      // earlier): ResNet-50 per layer at 0.6 % 94.4 / 96.6 us, 1 % 99.4 / 100.4, 3 % 116.7 / 112.4; BERT
-      // per layer 0.6 % 292.8 / 299.6, 1 % 297.5 / 291.5, 3 % 362.8 / 341.1.  Candidates under 1.8 k_l
-      // (large samples): from 0.5 % on.  Segments sampled whole have few winners either way (ResNet-50 per
+      // Without / with, per layer, in us (the larger layouts' e does not stay in the 256 MB of cache):
+      //   ResNet-50 (2.6e7 elements)  0.6 % 98.9 / 100.5, 1.2 % 103.5 / 104.0, 1.5 % 105.2 / 104.9, 2.5 % 112.7 / 110.8
+      //   BERT of 6.7e7               0.6 % 195.7 / 200.9, 1.2 % 207.1 / 207.5, 1.5 % 211.6 / 209.2, 2.5 % 229.8 / 219.7
+      //   BERT-base (1.1e8)           0.6 % 295.3 / 300.1, 0.9 % 302.6 / 305.4, 1.2 % 313.1 / 309.0, 2.5 % 354.0 / 332.9
+      // They cross at 1.2-1.5 % up to 6.7e7 elements and near 1 % from 8e7 on; between the line and the
+      // crossing the other form is at most 2 % better.  Candidates under 1.8 k_l (large samples): from
+      // 0.5 % on.  Segments sampled whole have few winners either way (ResNet-50 per
       // layer at 1 %, whose 4096-element layers would qualify: 110.7 / 114.1).
       const double dense = (double)off64[n] > 67108864.0 ? 0.009 : 0.015;
       zc[l] = dl > kExactMax && (kl >= dense * dl || (kl >= 0.005 * dl && et <= 1.8 * kl)) ? 1u : 0u;
@@ -729,10 +732,11 @@ int run_select(const ef_layout* L, const Steps& P, unsigned phases, void* stream
     if (one) EF_LAUNCH((k_emit<KIND, RW, true>), egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);          \
     else EF_LAUNCH((k_emit<KIND, RW, false>), egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);             \
   } while (0)
-    if (emit_rw == 16u) EF_EMIT(16);
-    else if (emit_rw == 8u) EF_EMIT(8);
-    else if (emit_rw == 4u) EF_EMIT(4);
-    else if (emit_rw == 2u) EF_EMIT(2);
+    constexpr uint32_t kMost = KIND == 1 ? 16u : 4u;  // (top-k: no form of more rows)
+    if (emit_rw == 16u) EF_EMIT(kMost);
+    else if (emit_rw == 8u) EF_EMIT((kMost < 8u ? kMost : 8u));
+    else if (emit_rw == 4u) EF_EMIT(4u);
+    else if (emit_rw == 2u) EF_EMIT(2u);
     else EF_LAUNCH(k_emit_row<KIND>, egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);
 #undef EF_EMIT
     EF_TRY(launched());
