@@ -732,11 +732,13 @@ int run_select(const ef_layout* L, const Steps& P, unsigned phases, void* stream
     if (one) EF_LAUNCH((k_emit<KIND, RW, true>), egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);          \
     else EF_LAUNCH((k_emit<KIND, RW, false>), egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);             \
   } while (0)
-    constexpr uint32_t kMost = KIND == 1 ? 16u : 4u;  // (top-k: no form of more rows)
-    if (emit_rw == 16u) EF_EMIT(kMost);
-    else if (emit_rw == 8u) EF_EMIT((kMost < 8u ? kMost : 8u));
-    else if (emit_rw == 4u) EF_EMIT(4u);
-    else if (emit_rw == 2u) EF_EMIT(2u);
+    if (emit_rw > 4u) {  // (random-k only)
+      if constexpr (KIND == 1) {
+        if (emit_rw == 16u) EF_EMIT(16);
+        else EF_EMIT(8);
+      }
+    } else if (emit_rw == 4u) EF_EMIT(4);
+    else if (emit_rw == 2u) EF_EMIT(2);
     else EF_LAUNCH(k_emit_row<KIND>, egrid, blk, 0, st, T, w, idx, val, bt, cz, brows);
 #undef EF_EMIT
     EF_TRY(launched());
