@@ -253,18 +253,20 @@ void ef_layout::build() {
       // top-k residual.  Single words written into evicted lines cost a line read and a line write each, so
       // on sampled segments that send much the pass stores +0 itself, at keys from R_Z on, the middle of
       // where the k_l-th key is expected; the emission then writes only where that middle missed (losers
-      // above it, winners below: a few percent of k_l).  Against +0 stored at all candidates: BERT per
-      // layer at 10 % 593 -> 447 us, flat at 10 % 392 -> 378.  Segments that send less keep a pass
+      // above it, winners below: a few percent of k_l with the large samples).  Against +0 stored at all
+      // candidates: BERT per layer at 10 % 593 -> 447 us, flat at 10 % 392 -> 378.  Segments that send less keep a pass
       // without the test where no other segment needs it, +0 being stored at the winners by the emission.
-      // Without / with, per layer, in us (the larger layouts' e does not stay in the 256 MB of cache):
-      //   ResNet-50 (2.6e7 elements)  0.6 % 98.9 / 100.5, 1.2 % 103.5 / 104.0, 1.5 % 105.2 / 104.9, 2.5 % 112.7 / 110.8
-      //   BERT of 6.7e7               0.6 % 195.7 / 200.9, 1.2 % 207.1 / 207.5, 1.5 % 211.6 / 209.2, 2.5 % 229.8 / 219.7
-      //   BERT-base (1.1e8)           0.6 % 295.3 / 300.1, 0.9 % 302.6 / 305.4, 1.2 % 313.1 / 309.0, 2.5 % 354.0 / 332.9
-      // They cross at 1.2-1.5 % up to 6.7e7 elements and near 1 % from 8e7 on; between the line and the
-      // crossing the other form is at most 2 % better.  Candidates under 1.8 k_l (large samples): from
-      // 0.5 % on.  Segments sampled whole have few winners either way (ResNet-50 per
-      // layer at 1 %, whose 4096-element layers would qualify: 110.7 / 114.1).
-      const double dense = (double)off64[n] > 67108864.0 ? 0.009 : 0.015;
+      // Without / with, one worker's step per layer in us, on Laplace gradients that change from step to
+      // step and (SAME) on gradients that stay the same, whose residual gathers below the threshold and
+      // makes the middle miss by more:
+      //   ResNet-50 (2.6e7 elements)  0.6 % 98.9 / 100.5, 1.25 % 104.2 / 104.5, 1.75 % 107.5 / 106.5, 2.5 % 112.7 / 110.8
+      //     SAME                      1.25 % 106.3 / 108.0, 1.75 % 109.4 / 109.6, 2 % 111.9 / 110.7, 3 % 117.4 / 113.1
+      //   BERT-base (1.1e8)           1 % 306.2 / 308.0, 1.25 % 315.3 / 311.2, 1.75 % 328.4 / 318.9, 2.5 % 354.0 / 332.9
+      //     SAME                      1 % 314 / 333, 1.25 % 323 / 335, 1.5 % 330 / 333, 1.75 % 333 / 332, 3 % 368 / 337
+      // (16 workers on such BERT-base gradients cross below 1.5 %: 1.25 % 5.56 / 5.73 ms, 1.75 % 5.88 / 5.65.)
+      // Candidates under 1.8 k_l (large samples): from 0.5 % on.  Segments sampled whole have few winners
+      // either way (ResNet-50 per layer at 1 %, whose 4096-element layers would qualify: 110.7 / 114.1).
+      const double dense = (double)off64[n] > 67108864.0 ? 0.0125 : 0.015;
       zc[l] = dl > kExactMax && (kl >= dense * dl || (kl >= 0.005 * dl && et <= 1.8 * kl)) ? 1u : 0u;
       const double mu = (double)tau[l] / 4294967296.0 * dl;
       const uint64_t cr = (uint64_t)std::min(dl, std::ceil(mu + 8.0 * std::sqrt(mu) + 64.0));
