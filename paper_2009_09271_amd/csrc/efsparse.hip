@@ -251,22 +251,23 @@ void ef_layout::build() {
       }
       const uint64_t ct = dl <= kExactMax ? (uint64_t)kl : (uint64_t)std::min(dl, std::ceil(2.0 * et + 8.0 * kl + 256.0));
       // top-k residual.  Single words written into evicted lines cost a line read and a line write each, so
-      // on sampled segments that send much the pass stores +0 itself, at keys from R_Z on, the middle of
-      // where the k_l-th key is expected; the emission then writes only where that middle missed (losers
-      // above it, winners below: a few percent of k_l with the large samples).  Against +0 stored at all
-      // candidates: BERT per layer at 10 % 593 -> 447 us, flat at 10 % 392 -> 378.  Segments that send less keep a pass
-      // without the test where no other segment needs it, +0 being stored at the winners by the emission.
-      // Without / with, one worker's step per layer in us, on Laplace gradients that change from step to
-      // step and (SAME) on gradients that stay the same, whose residual gathers below the threshold and
-      // makes the middle miss by more:
-      //   ResNet-50 (2.6e7 elements)  0.6 % 98.9 / 100.5, 1.25 % 104.2 / 104.5, 1.75 % 107.5 / 106.5, 2.5 % 112.7 / 110.8
-      //     SAME                      1.25 % 106.3 / 108.0, 1.75 % 109.4 / 109.6, 2 % 111.9 / 110.7, 3 % 117.4 / 113.1
-      //   BERT-base (1.1e8)           1 % 306.2 / 308.0, 1.25 % 315.3 / 311.2, 1.75 % 328.4 / 318.9, 2.5 % 354.0 / 332.9
-      //     SAME                      1 % 314 / 333, 1.25 % 323 / 335, 1.5 % 330 / 333, 1.75 % 333 / 332, 3 % 368 / 337
-      // (16 workers on such BERT-base gradients cross below 1.5 %: 1.25 % 5.56 / 5.73 ms, 1.75 % 5.88 / 5.65.)
-      // Candidates under 1.8 k_l (large samples): from 0.5 % on.  Segments sampled whole have few winners
-      // either way (ResNet-50 per layer at 1 %, whose 4096-element layers would qualify: 110.7 / 114.1).
-      const double dense = (double)off64[n] > 67108864.0 ? 0.0125 : 0.015;
+      // on sampled segments that send much the pass stores +0 itself, at keys from R_Z on, near where the
+      // k_l-th key is expected; the emission then writes only where that missed (losers above it, winners
+      // below: a few percent of k_l with the large samples, a quarter where ten samples lie above it).
+      // Against +0 stored at all candidates: BERT per layer at 10 % 593 -> 447 us, flat at 10 % 392 -> 378.
+      // Segments that send less keep a pass without the test where no other segment needs it, +0 being
+      // stored at the winners by the emission.  Without / with, one worker's step per layer in us, on
+      // Laplace gradients that change from step to step and (SAME) on gradients that stay the same, whose
+      // residual gathers below the threshold:
+      //   ResNet-50 (2.6e7 elements)  0.6 % 99.0 / 100.0, 1 % 101.8 / 101.4, 1.25 % 104.4 / 103.0, 3 % 116.1 / 108.2
+      //     SAME                      1 % 103.6 / 104.7, 1.25 % 106.5 / 106.9, 1.75 % 109.7 / 107.1, 3 % 117.6 / 110.0
+      //   BERT-base (1.1e8)           0.8 % 301.0 / 305.8, 1 % 307.0 / 307.1, 1.25 % 315.4 / 310.3, 3 % 363.5 / 319.8
+      //     SAME                      0.6 % 301.6 / 312.6, 1 % 314.0 / 319.9, 1.5 % 329.3 / 325.3, 3 % 365.5 / 329.3
+      // Batches gain earlier (16 workers at 1 %, SAME: BERT-base 5.32 / 5.18 ms, ResNet-50 1.46 / 1.42;
+      // 3 workers on Laplace gradients 888 / 866 us).  Candidates under 1.8 k_l (large samples): from 0.5 %
+      // on.  Segments sampled whole have few winners either way (ResNet-50 per layer at 1 %, whose
+      // 4096-element layers would qualify: 110.7 / 114.1).
+      const double dense = (double)off64[n] > 67108864.0 ? 0.0095 : 0.0125;
       zc[l] = dl > kExactMax && (kl >= dense * dl || (kl >= 0.005 * dl && et <= 1.8 * kl)) ? 1u : 0u;
       const double mu = (double)tau[l] / 4294967296.0 * dl;
       const uint64_t cr = (uint64_t)std::min(dl, std::ceil(mu + 8.0 * std::sqrt(mu) + 64.0));
