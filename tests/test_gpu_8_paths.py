@@ -223,8 +223,9 @@ def test_randk_wide_lists_hold_two_wavefronts():
 
 
 # top-k, a layout of several segments: +0 stored by the pass or by the emission (the densities on both sides of
-# the rule; few samples above the threshold and many), segments sampled whole among them, and one of few magnitudes: at most of the densities
-# its threshold is the smallest candidate key and shared by more elements than win, with candidates above it
+# the rule; few samples above the threshold and many), segments sampled whole among them, and one of few
+# magnitudes: its threshold is the smallest candidate key and shared by more elements than win, with
+# candidates above it
 @pytest.mark.parametrize("density", [0.004, 0.012, 0.013, 0.3])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_topk_residual_store(density, dtype):
